@@ -9,23 +9,34 @@
 //   V: [L][Hkv][D] -> v_pool[phys][h][:][slot]        (transposed per block)
 // with phys = table[(P + t) / bs] and slot = (P + t) % bs.
 //
-// One workgroup moves 32 positions of one KV head, one 16-byte chunk of K and
-// one of V per thread (D / 8 threads per position: 512 threads for D = 128):
-// many small workgroups keep more of the chip's load queues busy than a few
-// large ones.  Each thread issues both loads first (the pools may alias
-// nothing the loads read, but the compiler cannot know that, so a load placed
-// after a store would wait for it), writes its K chunk out as one 16-byte
-// store and scatters its V chunk into an LDS tile [D][32 positions].  After
-// one barrier the tile leaves as 16-byte stores of 8 consecutive slots of one
-// head-dim row (a whole 32-aligned tile), or 2-byte stores at ragged edges.
+// The kernel is bound by HBM (8 * len * Hkv * D bytes) and, below a few
+// thousand positions, by latency.  One workgroup moves the positions of one
+// KV head that fall into one 64-slot tile of the store, aligned to the tile:
+// wherever a chunk starts, only its first and last tile are partial, one block
+// holds the whole tile, and V leaves in whole 128-byte lines (64 slots of one
+// head-dim row).  Tiles counted from the chunk's start instead left every tile
+// of a chunk that starts off the grid to 2-byte stores.  Measured (kernel
+// time, inputs not in cache): 20011 positions from 8191, 8 heads of 128:
+// 53.9 -> 36.1 us (3.0 -> 4.5 TB/s; a large device copy reaches 5.2); 2048
+// positions on the grid: 5.0 -> 5.1 us (tiles of 32 positions: 38.1 and
+// 5.0 us; half or a quarter of the threads with more loads each: 36 and
+// 5.2-7.1 us).
+//
+// One 16-byte chunk of K and one of V per thread (D / 8 threads per position).
+// Each thread issues both loads first (the pools may alias nothing the loads
+// read, but the compiler cannot know that, so a load placed after a store
+// would wait for it), writes its K chunk out as one 16-byte store and scatters
+// its V chunk into an LDS tile [D][64 positions].  After one barrier the tile
+// leaves as 16-byte stores of 8 consecutive slots of one head-dim row, or
+// 2-byte stores where a group of 8 slots is not all the chunk's.
 //
 // LDS tile: 16-byte chunk (e, q) holds positions 8q .. 8q+7 of dim e and is
-// stored at chunk slot (4 e + q) ^ ((e / 8) % 16).  For D = 128 a 2-byte
+// stored at chunk slot (8 e + q) ^ ((e / 8) % 16).  For D = 128 a 2-byte
 // write instruction (16 chunk columns ch, dims e = 8 ch + k, positions
 // t, t+2, t+4, t+6) then lands in 16 distinct groups of four banks, one
 // dword of each bank, and the 16 lanes that a 16-byte read serves at a time
-// (chunks 16 m .. 16 m + 15) stay in distinct groups too: no bank conflicts.
-// (D = 64 has 8 chunk columns and writes two lanes per bank.)
+// (dims e and e + 1 with e even, all q) stay in distinct groups too: no bank
+// conflicts.  (D = 64 has 8 chunk columns and writes two lanes per bank.)
 #include "internal.h"
 
 namespace mocap {
@@ -33,34 +44,33 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kAppendTokens = 32;  // positions per workgroup (4 chunks of 8 per dim row)
+constexpr int kAppendTokens = 64;  // slots per workgroup, aligned (divides every block size)
 
 template <int D>
 constexpr int append_threads() { return kAppendTokens * (D / 8); }
 
 // Element index of (dim e, position tok) in the tile.
 __device__ __forceinline__ int v_index(int e, int tok) {
-  return ((((e << 2) + (tok >> 3)) ^ ((e >> 3) & 15)) << 3) + (tok & 7);
+  return (((e * (kAppendTokens / 8) + (tok >> 3)) ^ ((e >> 3) & 15)) << 3) + (tok & 7);
 }
 
 template <int D>
 __global__ __launch_bounds__(append_threads<D>()) void kv_append_kernel(const AppendLaunch p) {
   constexpr int T = kAppendTokens;
   constexpr int ROW_CHUNKS = D / 8;  // 16-byte chunks per position
-  constexpr int NT = append_threads<D>();
   __shared__ __attribute__((aligned(16))) uint16_t vt[D * T];
 
   const int tid = threadIdx.x;
-  const int t0 = blockIdx.x * T;
   const int h = blockIdx.y;
-  const int n_tok = min(T, p.chunk_len - t0);
-  const int64_t pos0 = p.start_pos + t0;
-  // The 32 positions span at most two blocks (block_size is a multiple of 64).
-  const int64_t lb0 = pos0 / p.block_size;
-  const int64_t slot00 = pos0 - lb0 * p.block_size;
-  const int split = (int)min<int64_t>(p.block_size - slot00, T);  // positions [0, split) in lb0
-  const int64_t phys0 = p.table[lb0];
-  const int64_t phys1 = split < n_tok ? (int64_t)p.table[lb0 + 1] : phys0;
+  // Absolute positions [tile0, tile0 + T) with tile0 a multiple of T: one
+  // block holds them (block_size is a multiple of 64).  Tile slots
+  // [first, last) belong to the chunk.
+  const int64_t tile0 = (p.start_pos / T + blockIdx.x) * T;
+  const int first = (int)max(p.start_pos - tile0, (int64_t)0);
+  const int last = (int)min(p.start_pos + p.chunk_len - tile0, (int64_t)T);
+  const uint32_t lb = (uint32_t)tile0 / (uint32_t)p.block_size;
+  const int64_t slot0 = tile0 - (int64_t)lb * p.block_size;
+  const int64_t head_row = (int64_t)p.table[lb] * p.h_kv + h;
 
   // Thread -> (position, chunk): the D / 8 lanes of a position read its
   // whole K and V rows, consecutive 16-byte pieces.  A wavefront takes every
@@ -69,13 +79,11 @@ __global__ __launch_bounds__(append_threads<D>()) void kv_append_kernel(const Ap
   constexpr int PW = 64 / ROW_CHUNKS;  // positions per wavefront
   const int wv = tid >> 6, wl = tid & 63;
   const int tok = (wv >> 1) * 2 * PW + (wv & 1) + 2 * (wl / ROW_CHUNKS), ch = wl % ROW_CHUNKS;
-  if (tok < n_tok) {
-    const int64_t src = ((int64_t)(t0 + tok) * p.h_kv + h) * D + ch * 8;
+  if (tok >= first && tok < last) {
+    const int64_t src = ((tile0 + tok - p.start_pos) * p.h_kv + h) * D + ch * 8;
     const u32x4 kr = *reinterpret_cast<const u32x4*>(p.k_chunk + src);
     const u32x4 vr = *reinterpret_cast<const u32x4*>(p.v_chunk + src);
-    const int64_t phys = tok < split ? phys0 : phys1;
-    const int64_t slot = tok < split ? slot00 + tok : tok - split;
-    *reinterpret_cast<u32x4*>(p.k_pool + ((phys * p.h_kv + h) * p.block_size + slot) * D + ch * 8) = kr;
+    *reinterpret_cast<u32x4*>(p.k_pool + (head_row * p.block_size + slot0 + tok) * D + ch * 8) = kr;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       const int e = ch * 8 + 2 * w;
@@ -85,29 +93,23 @@ __global__ __launch_bounds__(append_threads<D>()) void kv_append_kernel(const Ap
   }
   __syncthreads();
 
-  if (n_tok == T && slot00 % T == 0) {
-    // A whole aligned tile (one block holds it): thread -> (dim row e, chunk
-    // q), 8 consecutive slots of one head-dim row per 16-byte store.
-    uint16_t* base = p.v_pool + (phys0 * p.h_kv + h) * D * (int64_t)p.block_size + slot00;
-    const int e = tid / (T / 8), q = tid % (T / 8);
-    const u32x4 out = *reinterpret_cast<const u32x4*>(vt + v_index(e, q * 8));
-    *reinterpret_cast<u32x4*>(base + (int64_t)e * p.block_size + q * 8) = out;
-    return;
-  }
-  // Otherwise (ragged edges): thread -> (position, one of NT / T dim rows).
-  const int lt = tid % T, lr = tid / T;
-  if (lt < n_tok) {
-    const int64_t phys = lt < split ? phys0 : phys1;
-    const int64_t slot = lt < split ? slot00 + lt : lt - split;
-    uint16_t* dst = p.v_pool + (phys * p.h_kv + h) * D * (int64_t)p.block_size + slot;
-    for (int e = lr; e < D; e += NT / T) dst[(int64_t)e * p.block_size] = vt[v_index(e, lt)];
+  // Thread -> (dim row e, group of 8 slots).
+  const int e = tid / (T / 8), slot = tid % (T / 8) * 8;
+  uint16_t* dst = p.v_pool + (head_row * D + e) * p.block_size + slot0 + slot;
+  const uint16_t* tile = vt + v_index(e, slot);
+  if (slot >= first && slot + 8 <= last) {
+    *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(tile);
+  } else {
+    for (int j = max(first - slot, 0); j < min(last - slot, 8); ++j) dst[j] = tile[j];
   }
 }
 
 }  // namespace
 
 hipError_t launch_kv_append(const AppendLaunch& p, int head_dim, hipStream_t stream) {
-  const dim3 grid((p.chunk_len + kAppendTokens - 1) / kAppendTokens, p.h_kv);
+  const int64_t first_tile = p.start_pos / kAppendTokens;
+  const int64_t end_tile = (p.start_pos + p.chunk_len + kAppendTokens - 1) / kAppendTokens;
+  const dim3 grid((unsigned)(end_tile - first_tile), p.h_kv);
   if (head_dim == 128) {
     hipLaunchKernelGGL(kv_append_kernel<128>, grid, dim3(append_threads<128>()), 0, stream, p);
   } else {

@@ -64,3 +64,24 @@ def test_empty_append_changes_nothing(gpu):
     binding.mocap_kv_append(store, table, 10, empty, empty)
     torch.cuda.synchronize()
     assert torch.equal(store.k_pool, before)
+
+
+@pytest.mark.parametrize("h_kv,d,bs", [(3, 128, 192), (2, 64, 64)])
+@pytest.mark.parametrize("start,n", [(0, 1), (7, 1), (8, 8), (63, 2), (1, 62), (5, 123), (64, 64), (60, 133), (191, 66)])
+def test_append_at_tile_edges(gpu, h_kv, d, bs, start, n):
+    """Chunks that start and end inside, at and across the 64-slot tiles and
+    the 8-slot groups in which V is stored; every other slot keeps its bits."""
+    blocks = (start + n + bs - 1) // bs
+    table = synth.permuted_table(blocks, 3, blocks + 1).cuda()
+    store = binding.KvStore(blocks + 1, bs, h_kv, d, fill=float("nan"))
+    want_k, want_v = store.k_pool.clone(), store.v_pool.clone()
+    _, k, v = synth.make_qkv(60 + start, n, 1, h_kv, d)
+    k, v = k.cuda(), v.cuda()
+    for t in range(n):
+        blk, slot = int(table[(start + t) // bs]), (start + t) % bs
+        want_k[blk, :, slot] = k[t]
+        want_v[blk, :, :, slot] = v[t]
+    binding.mocap_kv_append(store, table, start, k, v)
+    torch.cuda.synchronize()
+    assert torch.equal(store.k_pool.view(torch.int16), want_k.view(torch.int16))
+    assert torch.equal(store.v_pool.view(torch.int16), want_v.view(torch.int16))
