@@ -123,7 +123,8 @@ mocap_status mocap_kv_append(const mocap_kv_store* kv, const int32_t* block_tabl
  * Section 4.1).  num_splits is the number of ranges: 1 = unsplit (no
  * workspace), n >= 2 = the prefix [0, P_c) cut into n - 1 ranges on 64-key
  * tile boundaries plus the chunk's own keys as the last range, 0 = let the
- * library choose from the shape and the current device's compute-unit count.
+ * library choose from the shape and the current device's compute-unit count
+ * (unsplit, or all keys [0, P_c + L_c) cut evenly on 64-key tile boundaries).
  * A requested count is clamped to what the prefix allows (1 when P_c = 0).
  *
  *   splits_out  (may be NULL) the number of ranges that will be used

@@ -62,16 +62,17 @@ mocap_status device_cu_count(int* out) {
   return MOCAP_OK;
 }
 
-// Query heads per unit (four waves): 2 when the GQA group is even, else 1.
-int heads_per_unit(int group) { return group % 2 == 0 ? 2 : 1; }
+// Rows (token, query head of the KV head's group) of one unit of four waves.
+constexpr int kUnitRows = kAttnWaveRows * kAttnWaves / 2;
 
 struct Plan {
-  int hu;
   int row_groups;
   int pairs;
-  int base_wgs;      // workgroups of one KV range
+  int base_wgs;      // workgroups of one KV range when row groups are paired
+  int64_t units;     // size of the chunk (bounded by make_plan)
   int64_t prefix_tiles;
   int n_ranges;
+  bool own_range;    // the chunk's own keys are a range of their own (requested splits)
   size_t ws_bytes;
   // Prefix tiles [remote_begin, remote_end) come from a second store.
   int64_t remote_begin = 0, remote_end = 0;
@@ -85,102 +86,135 @@ size_t workspace_for(int n_ranges, int64_t chunk_len, int h_q, int head_dim) {
   return round_up(rows * (size_t)head_dim * sizeof(float), 256) + round_up(rows * sizeof(float), 256);
 }
 
-// Time model of one launch, used to choose the number of KV ranges.
-//   * A workgroup costs kTileUs per 64-key tile that both of its units
-//     compute and kLoneTile times that for a tile only its longer unit
-//     computes (one wave per SIMD), scaled by head_dim / 128, plus kGroupUs
-//     of fixed work; one workgroup per compute unit at a time (the attention
-//     kernel's LDS ring fills a CU).
-//   * The launch time is the makespan of longest-first list scheduling of
-//     all workgroups onto the compute units (the kernel orders its work items
-//     longest first), plus, when split, the partial-result traffic (written
-//     by the attention kernel, read by the merge) at kMergeBytesPerUs.
-// The constants were measured on MI355X; only the ranking of candidate
-// plans depends on them.
-constexpr double kTileUs = 2.0;
-constexpr double kGroupUs = 4.0;
-constexpr double kMergeBytesPerUs = 3.0e6;
-constexpr double kLaunchUs = 4.0;
-constexpr double kLoneTile = 0.65;
+// One attention launch as the planner sees it.
+struct LaunchShape {
+  int64_t prefix_len;
+  int32_t chunk_len, h_q, h_kv, head_dim;
+  int row_groups;
+  int slots;  // compute units
+};
 
-double estimate_launch_us(int64_t prefix_len, int32_t chunk_len, int h_q, int head_dim, int head_blocks_total,
-                          int row_groups, int rows_per_unit, int64_t prefix_tiles, int n_ranges, int slots,
-                          bool adjacent) {
-  std::vector<double> cost;
-  const int pairs = (row_groups + 1) / 2;
-  cost.reserve((size_t)head_blocks_total * pairs * n_ranges);
-  const double tile_us = kTileUs * head_dim / 128.0;
-  // Tiles the unit of row group rg visits in the range that holds the chunk's keys.
-  auto unit_tiles = [&](int rg) -> int64_t {
-    const int64_t row_end = std::min<int64_t>(chunk_len, (int64_t)(rg + 1) * rows_per_unit);
-    const int64_t t0 = n_ranges == 1 ? 0 : prefix_len / kTileKeys;
-    return (prefix_len + row_end + kTileKeys - 1) / kTileKeys - t0;
+// Time model of one launch, used to choose the KV ranges and the pairing.
+//   * A workgroup costs a tile time per 64-key tile that both of its units
+//     compute and kLoneTile times that for a tile only its longer unit
+//     computes (two waves share its rows' keys, or one wave per SIMD works),
+//     plus kGroupUs of fixed work; one workgroup per compute unit at a time
+//     (the attention kernel's LDS ring fills a CU).
+//   * The launch time is the makespan of the workgroups in the order the
+//     hardware hands them out: each XCD takes one contiguous run of the
+//     logical order and starts the next workgroup on whichever of its compute
+//     units is free (so a count just above a whole number per compute unit
+//     costs a second round: 39 workgroups per range on 256 compute units run
+//     at 75 us in 6 ranges and 109 us in 7).  Plus, when split, the merge: a
+//     launch and its traffic (the partials, written and read) at
+//     kMergeBytesPerUs.
+// The constants were measured on MI355X, on launches short enough that the
+// clock holds; only the ranking of candidate plans depends on them.
+constexpr double kTileUs128 = 1.25, kTileUs64 = 0.8;
+constexpr double kGroupUs = 6.0;
+constexpr double kMergeBytesPerUs = 5.0e6;
+constexpr double kLaunchUs = 6.0;
+constexpr double kLoneTile = 0.65;
+constexpr int kXcds = 8;
+// A workgroup's row groups (see AttnLaunch): single placements are looked at
+// up to this many workgroups per compute unit.
+using mocap::kAdjacent;
+using mocap::kMirrored;
+using mocap::kSingle;
+constexpr int64_t kSingleRounds = 2;
+
+// Estimates of `limit` or more may be returned early, from the mean load alone.
+double estimate_launch_us(const LaunchShape& x, int n_ranges, bool own_range, int pairing, double limit) {
+  const int group = x.h_q / x.h_kv;
+  const int pairs = mocap::wgs_of_row_groups(x.row_groups, pairing);
+  const double tile_us = x.head_dim == 128 ? kTileUs128 : kTileUs64;
+  const int64_t prefix_tiles = (x.prefix_len + kTileKeys - 1) / kTileKeys;
+  const int64_t all_tiles = (x.prefix_len + x.chunk_len + kTileKeys - 1) / kTileKeys;
+  const int parts = own_range ? n_ranges - 1 : n_ranges;
+  const int64_t span = own_range ? prefix_tiles : all_tiles;
+  // Tiles the unit of row group rg visits among tiles [t0, t1).
+  auto unit_tiles = [&](int rg, int64_t t0, int64_t t1) -> int64_t {
+    if (rg < 0) return 0;
+    const int64_t tokens = std::min<int64_t>(x.chunk_len, ((int64_t)(rg + 1) * kUnitRows + group - 1) / group);
+    const int64_t end = (x.prefix_len + tokens + kTileKeys - 1) / kTileKeys;
+    return std::max<int64_t>(0, std::min(t1, end) - t0);
   };
-  for (int q = 0; q < pairs; ++q) {
-    // Mirrored pair q: row groups q and R-1-q; adjacent pair q: R-2-2q and R-1-2q.
-    const int top = adjacent ? row_groups - 1 - 2 * q : row_groups - 1 - q;
-    const int other = adjacent ? top - 1 : q;
-    const int64_t a = unit_tiles(top);
-    const int64_t b = (other < 0 || other == top) ? 0 : unit_tiles(other);
-    const double us = (double)std::min(a, b) * tile_us + (double)(std::max(a, b) - std::min(a, b)) * kLoneTile * tile_us;
-    for (int hb = 0; hb < head_blocks_total; ++hb) cost.push_back(us + kGroupUs);
-  }
-  if (n_ranges > 1) {
-    const int parts = n_ranges - 1;
-    for (int r = 0; r < parts; ++r) {
-      const int64_t tiles = prefix_tiles * (r + 1) / parts - prefix_tiles * r / parts;
-      for (int i = 0; i < head_blocks_total * pairs; ++i) cost.push_back(tiles * tile_us + kGroupUs);
+  std::vector<double> cost;  // of one KV head, in logical order
+  cost.reserve((size_t)pairs * n_ranges);
+  for (int r = 0; r < n_ranges; ++r) {
+    const int64_t t0 = r < parts ? span * r / parts : x.prefix_len / kTileKeys;
+    const int64_t t1 = r < parts ? span * (r + 1) / parts : all_tiles;
+    for (int q = 0; q < pairs; ++q) {
+      // Pair q: row groups q and R-1-q, R-2-2q and R-1-2q, or R-1-q alone.
+      const int top = pairing == kAdjacent ? x.row_groups - 1 - 2 * q : x.row_groups - 1 - q;
+      const int other = pairing == kSingle ? -1 : pairing == kAdjacent ? top - 1 : q < top ? q : -1;
+      const int64_t a = unit_tiles(top, t0, t1), b = unit_tiles(other, t0, t1);
+      cost.push_back(((double)std::min(a, b) + (double)(std::max(a, b) - std::min(a, b)) * kLoneTile) * tile_us +
+                     kGroupUs);
     }
   }
-  std::sort(cost.begin(), cost.end(), std::greater<double>());
-  std::priority_queue<double, std::vector<double>, std::greater<double>> load;
-  for (int i = 0; i < slots; ++i) load.push(0.0);
-  double makespan = 0.0;
-  for (double c : cost) {
-    const double t = load.top() + c;
-    load.pop();
-    load.push(t);
-    makespan = std::max(makespan, t);
-  }
-  double total = makespan + kLaunchUs;
+  double fixed = kLaunchUs;
   if (n_ranges > 1) {
-    const double partial = (double)n_ranges * chunk_len * h_q * (head_dim + 1) * 4.0;
-    total += 2.0 * partial / kMergeBytesPerUs + kLaunchUs;
+    const double partial = (double)n_ranges * x.chunk_len * x.h_q * (x.head_dim + 1) * 4.0;
+    fixed += 2.0 * partial / kMergeBytesPerUs + kLaunchUs;
   }
-  return total;
+  const int64_t total_wgs = (int64_t)cost.size() * x.h_kv;
+  const int xcd_slots = std::max(1, x.slots / kXcds);
+  double sum = 0.0;
+  for (double c : cost) sum += c;
+  const double mean = sum * x.h_kv / (xcd_slots * kXcds);
+  if (fixed + mean >= limit) return fixed + mean;
+  double makespan = 0.0;
+  int64_t next = 0;
+  for (int xcd = 0; xcd < kXcds; ++xcd) {
+    const int64_t end = next + total_wgs / kXcds + (xcd < total_wgs % kXcds ? 1 : 0);
+    std::priority_queue<double, std::vector<double>, std::greater<double>> load;
+    for (int i = 0; i < xcd_slots; ++i) load.push(0.0);
+    for (; next < end; ++next) {
+      const double t = load.top() + cost[(size_t)(next % (int64_t)cost.size())];
+      load.pop();
+      load.push(t);
+      makespan = std::max(makespan, t);
+    }
+  }
+  return fixed + makespan;
 }
 
-// 0 = automatic pairing choice; MOCAP_PAIRING=mirrored (1) or adjacent (2).
+// MOCAP_PAIRING=mirrored, =adjacent or =single in the environment forces a
+// pairing (for tests); -1 = choose.
 int pairing_mode() {
   const char* force = std::getenv("MOCAP_PAIRING");
-  if (force && std::strcmp(force, "mirrored") == 0) return 1;
-  if (force && std::strcmp(force, "adjacent") == 0) return 2;
-  return 0;
+  if (force && std::strcmp(force, "mirrored") == 0) return kMirrored;
+  if (force && std::strcmp(force, "adjacent") == 0) return kAdjacent;
+  if (force && std::strcmp(force, "single") == 0) return kSingle;
+  return -1;
 }
 
-// The better of the two pairings of row groups in a workgroup (mirrored:
-// q with R-1-q, every workgroup about equally long, the shorter unit idle
-// for part of the diagonal; adjacent: 2q with 2q+1, both units busy nearly
-// throughout, workgroups of different lengths balanced by longest-first
-// scheduling when there are many per compute unit).  MOCAP_PAIRING=mirrored
-// or =adjacent in the environment forces one (for tests).
-double best_pairing_us(int64_t prefix_len, int32_t chunk_len, int h_q, int head_dim, int head_blocks_total,
-                       int row_groups, int rows_per_unit, int64_t prefix_tiles, int n_ranges, int slots,
-                       bool* adjacent_out) {
+// The best placement of row groups in workgroups (mirrored: q with R-1-q,
+// every workgroup about equally long, the units sharing the tiles only the
+// longer one sees; adjacent: 2q with 2q+1, both units on their own rows nearly
+// throughout, workgroups of different lengths evened out when there are many
+// per compute unit; single: both units on one row group's tiles, half of each
+// tile's keys, which pays where even then compute units stay free).
+double best_pairing_us(const LaunchShape& x, int n_ranges, bool own_range, double limit, int* pairing_out) {
   const int mode = pairing_mode();
-  const bool only_mirrored = mode == 1, only_adjacent = mode == 2;
-  const double mirrored = only_adjacent ? INFINITY
-                                        : estimate_launch_us(prefix_len, chunk_len, h_q, head_dim, head_blocks_total,
-                                                             row_groups, rows_per_unit, prefix_tiles, n_ranges, slots,
-                                                             false);
-  const double adjacent = only_mirrored ? INFINITY
-                                        : estimate_launch_us(prefix_len, chunk_len, h_q, head_dim, head_blocks_total,
-                                                             row_groups, rows_per_unit, prefix_tiles, n_ranges, slots,
-                                                             true);
-  // Adjacent only when the model expects it to win clearly.
-  const bool adj = only_adjacent || (!only_mirrored && adjacent < mirrored * 0.98);
-  if (adjacent_out) *adjacent_out = adj;
-  return adj ? adjacent : mirrored;
+  int best = mode >= 0 ? mode : kMirrored;
+  double best_us = estimate_launch_us(x, n_ranges, own_range, best, limit);
+  if (mode < 0 && x.row_groups > 1) {
+    // Another pairing only when the model expects it to win clearly.  With up
+    // to two row groups the two ways to pair them are the same.
+    for (int pairing : {kAdjacent, kSingle}) {
+      if (pairing == kAdjacent && x.row_groups <= 2) continue;
+      if (pairing == kSingle && (int64_t)x.row_groups * x.h_kv * n_ranges > kSingleRounds * (int64_t)x.slots) continue;
+      const double us = estimate_launch_us(x, n_ranges, own_range, pairing, std::min(limit, best_us * 0.98));
+      if (us < best_us * 0.98) {
+        best_us = us;
+        best = pairing;
+      }
+    }
+  }
+  if (pairing_out) *pairing_out = best;
+  return best_us;
 }
 
 struct PlanKey {
@@ -203,37 +237,46 @@ PlanKey g_plan_keys[kPlanCache];
 int g_plan_values[kPlanCache];
 int g_plan_count = 0, g_plan_next = 0;
 
+// Most workgroups of a split launch, and fewest tiles of a range.
+constexpr int64_t kSplitWgs = 4096;
+constexpr int64_t kMinRangeTiles = 4;
+
 // Number of KV ranges to use.  A requested count is clamped to what the
-// prefix allows; 0 picks, among the prefix cut into 1, 2, 4, 8 or 16 ranges
-// of at least 4 tiles (plus the chunk's own range) whose workspace fits in
-// ws_cap bytes, or no split at all, the plan with the smallest modelled
-// launch time.
-int choose_ranges(int64_t prefix_len, int32_t chunk_len, int h_q, int h_kv, int head_dim, int head_blocks_total,
-                  int row_groups, int rows_per_unit, int64_t prefix_tiles, int requested, int slots,
-                  size_t ws_cap) {
+// prefix allows (the chunk's own keys are then the last range).  0 picks the
+// plan with the smallest modelled launch time among no split and even cuts of
+// all keys whose workspace fits in ws_cap bytes: any count up to 16, and above
+// that the counts that fill the compute units a whole number of times.
+int choose_ranges(const LaunchShape& x, int base_wgs, int64_t prefix_tiles, int requested, size_t ws_cap) {
   if (prefix_tiles <= 0) return 1;
   if (requested >= 1) {
     if (requested == 1) return 1;
     const int64_t parts = requested - 1 < prefix_tiles ? requested - 1 : prefix_tiles;
     return (int)parts + 1;
   }
-  const PlanKey key{prefix_len, chunk_len, h_q, h_kv, head_dim, requested, slots, ws_cap, pairing_mode()};
+  const PlanKey key{x.prefix_len, x.chunk_len, x.h_q, x.h_kv, x.head_dim, requested, x.slots, ws_cap, pairing_mode()};
   {
     std::lock_guard<std::mutex> lock(g_plan_mutex);
     for (int i = 0; i < g_plan_count; ++i)
       if (g_plan_keys[i] == key) return g_plan_values[i];
   }
   int best = 1;
-  double best_us = best_pairing_us(prefix_len, chunk_len, h_q, head_dim, head_blocks_total, row_groups,
-                                   rows_per_unit, prefix_tiles, 1, slots, nullptr);
-  const int64_t max_parts = std::min<int64_t>(16, prefix_tiles / 4);
-  for (int64_t parts = 1; parts <= max_parts; parts *= 2) {
-    if (workspace_for((int)parts + 1, chunk_len, h_q, head_dim) > ws_cap) break;
-    const double us = best_pairing_us(prefix_len, chunk_len, h_q, head_dim, head_blocks_total, row_groups,
-                                      rows_per_unit, prefix_tiles, (int)parts + 1, slots, nullptr);
-    if (us < best_us * 0.98) {  // a split must pay for itself clearly
+  // A split must pay for itself clearly.
+  double best_us = 0.98 * best_pairing_us(x, 1, false, INFINITY, nullptr);
+  auto consider = [&](int64_t n) {
+    if (workspace_for((int)n, x.chunk_len, x.h_q, x.head_dim) > ws_cap) return;
+    const double us = best_pairing_us(x, (int)n, false, best_us, nullptr);
+    if (us < best_us) {
       best_us = us;
-      best = (int)parts + 1;
+      best = (int)n;
+    }
+  };
+  const int64_t all_tiles = (x.prefix_len + x.chunk_len + kTileKeys - 1) / kTileKeys;
+  const int64_t max_n = std::min(all_tiles / kMinRangeTiles, kSplitWgs / base_wgs);
+  for (int64_t n = 2; n <= std::min<int64_t>(16, max_n); ++n) consider(n);
+  for (int64_t k = 1; k * x.slots <= kSplitWgs; ++k) {
+    for (const int64_t wgs : {(int64_t)base_wgs, (int64_t)x.row_groups * x.h_kv}) {
+      const int64_t n = k * x.slots / wgs;
+      if (n > 16 && n <= max_n) consider(n);
     }
   }
   std::lock_guard<std::mutex> lock(g_plan_mutex);
@@ -246,22 +289,24 @@ int choose_ranges(int64_t prefix_len, int32_t chunk_len, int h_q, int h_kv, int 
 
 mocap_status make_plan(int64_t prefix_len, int32_t chunk_len, int32_t h_q, int32_t h_kv,
                        int32_t head_dim, int32_t num_splits, Plan* plan, size_t ws_cap = SIZE_MAX) {
-  const int group = h_q / h_kv;
-  plan->hu = heads_per_unit(group);
-  const int rows_per_unit = kAttnWaveRows * (kAttnWaves / 2 / plan->hu);
-  plan->row_groups = (int)((chunk_len + rows_per_unit - 1) / rows_per_unit);
+  const int64_t group = h_q / h_kv;
+  // The bound on a chunk's size: 2^24 pairs of 128-row units, counted per
+  // block of up to two query heads.
+  const int64_t hu = group % 2 == 0 ? 2 : 1;
+  plan->units = (h_q / hu) * ((((chunk_len * hu + kUnitRows - 1) / kUnitRows) + 1) / 2);
+  if (plan->units > (int64_t)1 << 24) return MOCAP_ERR_UNSUPPORTED;
+  plan->row_groups = (int)((chunk_len * group + kUnitRows - 1) / kUnitRows);
   plan->pairs = (plan->row_groups + 1) / 2;
-  const int64_t base = (int64_t)(h_q / plan->hu) * plan->pairs;
-  if (base > (int64_t)1 << 24) return MOCAP_ERR_UNSUPPORTED;
-  plan->base_wgs = (int)base;
+  plan->base_wgs = h_kv * plan->pairs;
   plan->prefix_tiles = (prefix_len + kTileKeys - 1) / kTileKeys;
   int cus = 0;
   if (num_splits == 0 && plan->prefix_tiles > 0) {
     const mocap_status st = device_cu_count(&cus);
     if (st != MOCAP_OK) return st;
   }
-  plan->n_ranges = choose_ranges(prefix_len, chunk_len, h_q, h_kv, head_dim, h_q / plan->hu, plan->row_groups,
-                                 rows_per_unit, plan->prefix_tiles, num_splits, cus, ws_cap);
+  const LaunchShape x{prefix_len, chunk_len, h_q, h_kv, head_dim, plan->row_groups, cus};
+  plan->n_ranges = choose_ranges(x, plan->base_wgs, plan->prefix_tiles, num_splits, ws_cap);
+  plan->own_range = num_splits > 1;
   plan->ws_bytes = workspace_for(plan->n_ranges, chunk_len, h_q, head_dim);
   return MOCAP_OK;
 }
@@ -314,34 +359,35 @@ bool valid_remote_range(int64_t begin, int64_t end, int64_t prefix_len) {
 struct PairKey {
   int64_t prefix_len;
   int32_t chunk_len, h_q, h_kv, head_dim, n_ranges, slots, mode;
+  bool own_range;
   bool operator==(const PairKey& o) const {
     return prefix_len == o.prefix_len && chunk_len == o.chunk_len && h_q == o.h_q && h_kv == o.h_kv &&
-           head_dim == o.head_dim && n_ranges == o.n_ranges && slots == o.slots && mode == o.mode;
+           head_dim == o.head_dim && n_ranges == o.n_ranges && slots == o.slots && mode == o.mode && own_range == o.own_range;
   }
 };
 PairKey g_pair_keys[kPlanCache];
-bool g_pair_values[kPlanCache];
+int g_pair_values[kPlanCache];
 int g_pair_count = 0, g_pair_next = 0;
 
-bool choose_pairing(const Plan& plan, int64_t prefix_len, int32_t chunk_len, int32_t h_q, int32_t h_kv,
+int choose_pairing(const Plan& plan, int64_t prefix_len, int32_t chunk_len, int32_t h_q, int32_t h_kv,
                     int32_t head_dim, int cus) {
-  if (plan.row_groups <= 2) return false;  // a single pair: both pairings are the same
-  const PairKey key{prefix_len, chunk_len, h_q, h_kv, head_dim, plan.n_ranges, cus, pairing_mode()};
+  if (plan.row_groups <= 1) return kMirrored;
+  const PairKey key{prefix_len, chunk_len, h_q, h_kv, head_dim, plan.n_ranges, cus, pairing_mode(),
+                    plan.own_range};
   {
     std::lock_guard<std::mutex> lock(g_plan_mutex);
     for (int i = 0; i < g_pair_count; ++i)
       if (g_pair_keys[i] == key) return g_pair_values[i];
   }
-  const int rows_per_unit = kAttnWaveRows * (kAttnWaves / 2 / plan.hu);
-  bool adjacent = false;
-  best_pairing_us(prefix_len, chunk_len, h_q, head_dim, h_q / plan.hu, plan.row_groups, rows_per_unit,
-                  plan.prefix_tiles, plan.n_ranges, std::max(cus, 1), &adjacent);
+  int pairing = kMirrored;
+  best_pairing_us(LaunchShape{prefix_len, chunk_len, h_q, h_kv, head_dim, plan.row_groups, std::max(cus, 1)},
+                  plan.n_ranges, plan.own_range, INFINITY, &pairing);
   std::lock_guard<std::mutex> lock(g_plan_mutex);
   g_pair_keys[g_pair_next] = key;
-  g_pair_values[g_pair_next] = adjacent;
+  g_pair_values[g_pair_next] = pairing;
   g_pair_next = (g_pair_next + 1) % kPlanCache;
   if (g_pair_count < kPlanCache) ++g_pair_count;
-  return adjacent;
+  return pairing;
 }
 
 // Launches the attention kernel (and the merge when the plan is split).
@@ -351,8 +397,7 @@ mocap_status enqueue_attention(const mocap_kv_store* kv, const int32_t* block_ta
                                const int32_t* remote_table, const Plan& plan, const void* q, int64_t prefix_len,
                                int32_t chunk_len, int32_t h_q, int32_t h_kv, int32_t head_dim, float scale,
                                void* o, float* lse, void* workspace, size_t workspace_bytes, void* stream) {
-  const int64_t total = (int64_t)plan.base_wgs * plan.n_ranges;
-  if (total > 0x7fffffff) return MOCAP_ERR_UNSUPPORTED;
+  if (plan.units * plan.n_ranges > 0x7fffffff) return MOCAP_ERR_UNSUPPORTED;
   if (plan.n_ranges > 1) {
     if (workspace == nullptr || !aligned16(workspace) || workspace_bytes < plan.ws_bytes)
       return MOCAP_ERR_WORKSPACE;
@@ -369,23 +414,27 @@ mocap_status enqueue_attention(const mocap_kv_store* kv, const int32_t* block_ta
   p.o = static_cast<uint16_t*>(o);
   p.lse = lse;
   p.prefix_len = (int32_t)prefix_len;
-  p.prefix_tiles = (int32_t)plan.prefix_tiles;
   p.chunk_len = chunk_len;
   p.h_q = h_q;
   p.h_kv = h_kv;
   p.group = h_q / h_kv;
-  p.heads_per_unit = plan.hu;
+  block_divider((uint32_t)p.group, &p.group_magic, &p.group_shift);
   p.row_groups = plan.row_groups;
-  p.pairs = plan.pairs;
   {
     int cus = 0;
     const mocap_status st = device_cu_count(&cus);
     if (st != MOCAP_OK) return st;
-    p.pair_adjacent = choose_pairing(plan, prefix_len, chunk_len, h_q, h_kv, head_dim, cus) ? 1 : 0;
+    p.pairing = choose_pairing(plan, prefix_len, chunk_len, h_q, h_kv, head_dim, cus);
   }
+  p.pairs = mocap::wgs_of_row_groups(plan.row_groups, p.pairing);
+  const int64_t total = (int64_t)p.pairs * h_kv * plan.n_ranges;
+  if (total > 0x7fffffff) return MOCAP_ERR_UNSUPPORTED;
   p.block_size = kv->block_size;
   block_divider((uint32_t)kv->block_size, &p.block_magic, &p.block_shift);
   p.n_ranges = plan.n_ranges;
+  p.span_parts = plan.own_range ? plan.n_ranges - 1 : plan.n_ranges;
+  p.span_end = (int32_t)(plan.own_range ? prefix_len : prefix_len + chunk_len);
+  p.span_tiles = (int32_t)(((int64_t)p.span_end + kTileKeys - 1) / kTileKeys);
   p.remote_begin = (int32_t)plan.remote_begin;
   p.remote_end = (int32_t)plan.remote_end;
   p.total_wgs = (int)total;

@@ -6,20 +6,29 @@
 //
 // Kernel structure
 //   * A workgroup is 8 wavefronts, two per SIMD, each within 256 registers.
-//     Each wavefront owns 32 query rows of one query head, kept in registers
-//     as the B operand of the score product.  All wavefronts of a workgroup
-//     share one KV head (GQA packing), so each K/V tile staged in LDS serves
-//     every query head of the group.
+//     Each wavefront owns 32 rows, kept in registers as the B operand of the
+//     score product.  The rows of a KV head are the (token, query head) pairs
+//     of its group in token-major order, so a chunk of L tokens fills
+//     ceil(L G / 32) wavefronts whatever G is, one K/V tile staged in LDS
+//     serves every query head of the group, and a wavefront's rows lie on
+//     32 / G neighbouring tokens, which keeps its masked tiles few.  With
+//     rows counted per query head instead (64 tokens of two heads per unit),
+//     137 tokens of 4 heads filled 137 of 256 slots, now 548 of 768:
+//     behind 30720 tokens 113 -> 90 us; 300 tokens behind 2^20 5.5 -> 4.7 ms;
+//     2048-token chunks within 0.5%.
 //   * Causal balance: the workgroup's two units of four waves take two row
-//     groups of the same query heads, r and R-1-r (mirrored, so every
-//     workgroup carries about the same number of (row, key) pairs) or two
-//     adjacent ones (when many workgroups per CU even out their lengths);
+//     groups of the same KV head, r and R-1-r (mirrored, so every
+//     workgroup carries about the same number of (row, key) pairs), two
+//     adjacent ones (when many workgroups per CU even out their lengths), or
+//     both one group (single, when there are compute units to spare: 256
+//     tokens of 8/8/64 heads behind 768 tokens 25.1 -> 18.3 us);
 //     the host picks per launch.  Each wave follows its own key range and
-//     treats the tiles all its rows see in full as unmasked.  In a mirrored
-//     pair, the last tiles only the longer row group sees are shared: the
-//     shorter group's wave stores its rows, takes over its partner's rows
-//     and computes the second 32-key half of each such tile while the
-//     partner computes the first; the two partial results meet in LDS.
+//     treats the tiles all its rows see in full as unmasked.  The last tiles
+//     of a mirrored pair that only the longer row group sees, and all tiles
+//     of a single group, are shared: the helping wave stores its own rows, if
+//     it has any, takes over its partner's rows and computes the second
+//     32-key half of each such tile while the partner computes the first; the
+//     two partial results meet in LDS.
 //   * K/V advance in tiles of 64 keys, copied global -> LDS directly
 //     (buffer_load_dwordx4 ... lds, no staging registers) into a 4-stage ring
 //     (128 KiB at head_dim 128), prefetched two tiles ahead, one workgroup
@@ -53,7 +62,7 @@
 //     tiles entirely above the diagonal are never visited.  Keys at or beyond
 //     P+L (unwritten store memory) are zero-filled in LDS so a probability of
 //     0 never meets a NaN.
-//   * Optional split of the prefix into ranges: each range writes normalised
+//   * Optional split of the keys into ranges: each range writes normalised
 //     fp32 partials and their log-sum-exp; lse_merge.hip combines them.
 //   * A run of prefix tiles may come from a second store (a debtor stage's
 //     remote KV portion, Section 4.1): the store is chosen per tile.
@@ -93,46 +102,56 @@ __device__ __forceinline__ int key_row_order(int m) {
 
 struct WorkItem {
   int kv_head;
-  int head0;        // first query head of both units
   int row_group_a;  // row group of waves 0-3
-  int row_group_b;  // row group of waves 4-7 (-1: none)
+  int row_group_b;  // row group of waves 4-7 (-1: none, unit B helps unit A)
   int range;        // KV range index
 };
 
 // Workgroup ids are handed to the 8 XCDs round robin.  Renumber them so each
 // XCD receives one contiguous run of logical items: consecutive items share a
 // KV head, so the tiles they stream stay in that XCD's L2.  Within a KV head
-// the logical order is range, then row-group pair (pair q holds row groups q
-// and R-1-q; the middle group of an odd R is alone), then the head blocks of
-// the group.
+// the logical order is range, then row-group pair.
 __device__ __forceinline__ WorkItem decode_item(const AttnLaunch& p, int hw_id) {
   const int n = p.total_wgs;
   const int xcd = hw_id & 7, slot = hw_id >> 3;
   const int per = n >> 3, rem = n & 7;
   const int logical = xcd * per + min(xcd, rem) + slot;
 
-  const int head_blocks = p.group / p.heads_per_unit;
-  const int per_range = head_blocks * p.pairs;
-  const int per_kv = per_range * p.n_ranges;
+  const int per_kv = p.pairs * p.n_ranges;
   WorkItem w;
   w.kv_head = logical / per_kv;
-  int r = logical - w.kv_head * per_kv;
-  w.range = r / per_range;
-  r -= w.range * per_range;
-  const int pair = r / head_blocks;
-  const int hb = r - pair * head_blocks;
-  // Unit A takes the lower row group of the pair, unit B the higher (-1: none).
-  if (p.pair_adjacent) {
+  const int r = logical - w.kv_head * per_kv;
+  w.range = r / p.pairs;
+  const int pair = r - w.range * p.pairs;
+  // Unit A takes the lower row group of the pair, unit B the higher; a group
+  // without a partner is unit A's.
+  if (p.pairing == kAdjacent) {
     const int top = p.row_groups - 1 - 2 * pair;
-    w.row_group_a = top > 0 ? top - 1 : top;
+    w.row_group_a = max(top - 1, 0);
     w.row_group_b = top > 0 ? top : -1;
   } else {
-    w.row_group_a = pair;
-    w.row_group_b = p.row_groups - 1 - pair;
-    if (w.row_group_b == pair) w.row_group_b = -1;
+    const int top = p.row_groups - 1 - pair;
+    const bool paired = p.pairing == kMirrored && pair < top;
+    w.row_group_a = paired ? pair : top;
+    w.row_group_b = paired ? top : -1;
   }
-  w.head0 = w.kv_head * p.group + hb * p.heads_per_unit;
   return w;
+}
+
+// The first row of 32-row slot s of a KV head: rows are the (token, query
+// head) pairs of the group in token-major order, so slot s starts at row 32 s:
+// token 32 s / G, head 32 s % G of the group.
+struct RowPos {
+  int token, head;
+};
+__device__ __forceinline__ uint32_t div_group(const AttnLaunch& p, uint32_t n) {
+  return (__umulhi(n, p.group_magic) + n) >> p.group_shift;
+}
+__device__ __forceinline__ RowPos slot_start(const AttnLaunch& p, int s) {
+  const int a = (int)div_group(p, s);
+  const int x = (s - a * p.group) * kAttnWaveRows;
+  const int t = (int)div_group(p, x);
+  return RowPos{a * kAttnWaveRows + t, x - t * p.group};
 }
 
 // Softmax bookkeeping.  Each query row keeps a reference exponent m (base 2)
@@ -225,82 +244,80 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_kernel(const AttnL
   const int P = p.prefix_len;
   const int L = p.chunk_len;
   // Waves 0-3 form unit A, waves 4-7 unit B (one wave of each per SIMD).
-  const int hu = p.heads_per_unit;
-  const int unit_rows = (kAttnWaves / 2 / hu) * kAttnWaveRows;
   const int uw = wave & 3;
-  const int head = item.head0 + (uw % hu);
   const bool unit_b = (wave >> 2) != 0;
-  // First row of this wave slot in row group rg, and whether any of its rows lies before L.
-  auto slot_row0 = [&](int rg) { return max(rg, 0) * unit_rows + (uw / hu) * kAttnWaveRows; };
-  auto slot_on = [&](int rg) { return rg >= 0 && rg * unit_rows + (uw / hu) * kAttnWaveRows < L; };
-  const int my_rg = unit_b ? item.row_group_b : item.row_group_a;
-  const bool wave_on = slot_on(my_rg);  // a wave whose rows all lie past L has nothing to do
-  int row0 = slot_row0(my_rg);
-  const int wg_row0 = item.row_group_a * unit_rows;
-  const int wg_row_end = min(L, (max(item.row_group_a, item.row_group_b) + 1) * unit_rows);
+  // The rows of this wave slot in row group rg start here; a wave whose rows
+  // all lie past L has none.
+  auto slot_rows = [&](int rg) { return slot_start(p, rg * 4 + uw); };
+  auto last_token = [&](RowPos r) { return min(L - 1, r.token + (int)div_group(p, r.head + kAttnWaveRows - 1)); };
+  const bool lone = item.row_group_b < 0;  // one row group: unit B starts on unit A's rows
+  const int top_group = max(item.row_group_a, item.row_group_b);
+  RowPos rows = slot_rows(unit_b ? top_group : item.row_group_a);
+  const bool wave_on = rows.token < L && !(lone && unit_b);
+  const int wg_token_end = last_token(slot_start(p, top_group * 4 + 3)) + 1;
 
   int lo, hi;
   if (p.n_ranges == 1) {
     lo = 0;
     hi = P + L;
-  } else if (item.range < p.n_ranges - 1) {
-    const int parts = p.n_ranges - 1;
-    lo = (int)((int64_t)p.prefix_tiles * item.range / parts) * kTileKeys;
-    hi = min((int)((int64_t)p.prefix_tiles * (item.range + 1) / parts) * kTileKeys, P);
+  } else if (item.range < p.span_parts) {
+    lo = (int)((int64_t)p.span_tiles * item.range / p.span_parts) * kTileKeys;
+    hi = min((int)((int64_t)p.span_tiles * (item.range + 1) / p.span_parts) * kTileKeys, p.span_end);
   } else {
     lo = P;
     hi = P + L;
   }
-  const int wg_hi = min(hi, P + wg_row_end);
+  const int wg_hi = min(hi, P + wg_token_end);
   const int tile_begin = lo / kTileKeys;
   const int tile_end = (wg_hi + kTileKeys - 1) / kTileKeys;
   const int valid_end = P + L;
-  const int n_head = (lo % kTileKeys) != 0 ? 1 : 0;
-  const int fast_begin = tile_begin + n_head;
-  const int fast_end = max(fast_begin, min(tile_end, min(hi, P + wg_row0 + 1) / kTileKeys));
-  const int n_fast = fast_end - fast_begin;
   const int n_tiles = tile_end - tile_begin;
-  auto seq_tile = [&](int i) __attribute__((always_inline)) -> int {
-    if (i < n_fast) return fast_begin + i;
-    if (i < n_fast + n_head) return tile_begin;
-    return fast_end + (i - n_fast - n_head);
+  auto seq_tile = [&](int i) __attribute__((always_inline)) -> int { return tile_begin + i; };
+  // A wave's share of the sequence: the first n positions, the tiles its rows
+  // see.
+  auto share_of = [&](RowPos r) {
+    const int w_tile_end = (min(hi, P + last_token(r) + 1) + kTileKeys - 1) / kTileKeys;
+    return r.token < L ? max(0, w_tile_end - tile_begin) : 0;
   };
-  // A wave's share of the sequence: the first n positions (the tiles its
-  // rows see; tiles past them come last in the order above), and, among
-  // them, the tiles every one of its rows sees in full (unmasked).
-  auto share_of = [&](int r0, bool on) {
-    const int w_tile_end = (min(hi, P + r0 + kAttnWaveRows) + kTileKeys - 1) / kTileKeys;
-    return on ? n_tiles - max(0, tile_end - w_tile_end) : 0;
-  };
-  const int n_w = share_of(row0, wave_on);
-  int w_full_end = min(hi, P + row0 + 1);
-  // Mirrored pairs leave the unit with the shorter row group idle on the
-  // last positions, which only the other unit's rows see.  When there are
-  // at least kHelpTiles of them, the wave of the shorter unit moves over to
-  // its partner's rows for those positions (the same wave slot of the other
-  // unit: same head, same SIMD): the partner computes the first 32-key half
-  // of each such tile, the helper the second, and the two partial results
-  // are merged through LDS at the end.  Both waves derive the same plan.
-  constexpr int kHelpTiles = 4;
-  const bool merge_wg = !p.pair_adjacent && item.row_group_b >= 0;
-  const int a_n_w = share_of(slot_row0(item.row_group_a), slot_on(item.row_group_a));
-  const int partner_row0 = slot_row0(item.row_group_b);
-  const int partner_n_w = share_of(partner_row0, slot_on(item.row_group_b));
-  const bool help = merge_wg && partner_n_w - a_n_w >= kHelpTiles;
-  const int help_from = a_n_w;
+  const int n_w = wave_on ? share_of(rows) : 0;
+  int w_full_end = min(hi, P + rows.token + 1);
+  // Mirrored pairs leave unit A, which has the shorter row group, idle on the
+  // last positions, which only unit B's rows see.  When there are at least
+  // kHelpTiles of them, its wave moves over to its partner's rows for those
+  // positions (the same wave slot of the other unit, on the same SIMD): the
+  // partner computes the first 32-key half of each such tile, the helper the
+  // second, and the two partial results are merged through LDS at the end.
+  // Both waves derive the same plan.  In a workgroup with one row group unit
+  // B helps unit A from the first position on, if there are at least
+  // kLoneHelpTiles: below that the merge costs more than the halves save
+  // (5 tiles: 13.7 us helped, 13.0 us alone; 15 tiles: 17.0 and 16.9 us).
+  constexpr int kHelpTiles = 4, kLoneHelpTiles = 8;
+  const bool merge_wg = p.pairing != kAdjacent || lone;
+  const int help_from = lone ? 0 : share_of(slot_rows(item.row_group_a));
+  const int top_n_w = share_of(slot_rows(top_group));
+  const bool help = merge_wg && top_n_w - help_from >= (lone ? kLoneHelpTiles : kHelpTiles);
+  const bool helper = unit_b == lone;  // this unit helps, if there is help
   auto masked_at = [&](int i) __attribute__((always_inline)) -> bool {
     const int t = seq_tile(i);
     return t * kTileKeys < lo || (t + 1) * kTileKeys > w_full_end;
   };
 
+  // This lane's row among the current 32: its token, and its head of the group.
+  auto lane_row = [&]() __attribute__((always_inline)) {
+    const int x = rows.head + l32;
+    const int t = (int)div_group(p, x);
+    return RowPos{rows.token + t, x - t * p.group};
+  };
   // Q fragments of the current 32 rows (B operand of S^T = K Q^T).
+  const int head0 = item.kv_head * p.group;
   bf16x8 qf[KS];
   auto load_q = [&]() __attribute__((always_inline)) {
-    const int row = row0 + l32;
+    const RowPos r = lane_row();
+    const uint16_t* qrow = p.q + ((int64_t)r.token * p.h_q + head0 + r.head) * D;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      if (row < L) {
-        qf[ks] = *reinterpret_cast<const bf16x8*>(p.q + ((int64_t)row * p.h_q + head) * D + ks * 16 + half * 8);
+      if (r.token < L) {
+        qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16 + half * 8);
       } else {
         qf[ks] = bf16x8{};
       }
@@ -386,7 +403,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_kernel(const AttnL
 
   auto visible_bits = [&](int base) __attribute__((always_inline)) -> uint32_t {
     const int a = lo - base;
-    const int b = min(hi, P + row0 + l32 + 1) - base;
+    const int b = min(hi, P + lane_row().token + 1) - base;
     auto first_i = [](int x) { return x <= 0 ? 0 : x <= 8 ? x : x <= 16 ? 8 : x <= 24 ? x - 8 : 16; };
     const int i0 = first_i(a), i1 = first_i(b);
     return i1 > i0 ? (((1u << i1) - 1u) & ~((1u << i0) - 1u)) : 0u;
@@ -742,12 +759,13 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_kernel(const AttnL
   auto store_outputs = [&]() __attribute__((always_inline)) {
     const float l_tot = lane_pair_sum(l_run);
     const float f_tot = lane_pair_sum(f_run);
-    const int row = row0 + l32;
-    if (row < L) {
+    const RowPos r = lane_row();
+    if (r.token < L) {
+      const int head = head0 + r.head;
       const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
       const float row_lse = f_tot > 0.f ? (m_run + log2f(f_tot)) * kLn2 : -INFINITY;
       if (!split) {
-        uint16_t* orow = p.o + ((int64_t)row * p.h_q + head) * D;
+        uint16_t* orow = p.o + ((int64_t)r.token * p.h_q + head) * D;
 #pragma unroll
         for (int md = 0; md < MD; ++md) {
 #pragma unroll
@@ -758,9 +776,9 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_kernel(const AttnL
             *reinterpret_cast<bf16x4*>(orow + md * 32 + j * 8 + half * 4) = v;
           }
         }
-        if (half == 0) p.lse[(int64_t)head * L + row] = row_lse;
+        if (half == 0) p.lse[(int64_t)head * L + r.token] = row_lse;
       } else {
-        const int64_t base = ((int64_t)item.range * p.h_q + head) * L + row;
+        const int64_t base = ((int64_t)item.range * L + r.token) * p.h_q + head;
         float* orow = p.ws_o + base * D;
 #pragma unroll
         for (int md = 0; md < MD; ++md) {
@@ -803,18 +821,18 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_kernel(const AttnL
       done = full_end;
     }
     if (help) {
-      if (!unit_b) {
-        if (full_end > 0) store_outputs();
-        row0 = partner_row0;
-        w_full_end = min(hi, P + row0 + 1);
+      if (helper && !lone) {
+        if (wave_on) store_outputs();
+        rows = slot_rows(item.row_group_b);
+        w_full_end = min(hi, P + rows.token + 1);
         load_q();
         m_run = -INFINITY;
         l_run = f_run = 0.f;
 #pragma unroll
         for (int md = 0; md < MD; ++md) oacc[md] = f32x16{};
       }
-      run_range(nh1, help_from, partner_n_w, unit_b ? 0 : 1);
-      done = partner_n_w;
+      run_range(nh1, help_from, top_n_w, helper ? 1 : 0);
+      done = top_n_w;
     }
     if (done == 0) {
       barrier_k(0);
@@ -830,7 +848,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_kernel(const AttnL
     constexpr int NV = MD * 16;
     float* mb = reinterpret_cast<float*>(lds) + uw * (NV + 3) * 64;
     lds_barrier();
-    if (help && !unit_b) {
+    if (help && helper) {
 #pragma unroll
       for (int md = 0; md < MD; ++md)
 #pragma unroll
@@ -842,7 +860,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_kernel(const AttnL
       mb[NV * 64 + 128 + lane] = f_run;
     }
     lds_barrier();
-    if (help && unit_b) {
+    if (help && !helper) {
       const float m_a = mb[NV * 64 + lane];
       const float m = fmaxf(m_run, m_a);
       const float cb = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
@@ -862,7 +880,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_kernel(const AttnL
   }
   // Waves with rows left to write: their own (no help), or the partner's
   // merged rows (the wave that was helped); a helping wave stored its own.
-  if (help ? unit_b : wave_on) store_outputs();
+  if (help ? !helper : wave_on) store_outputs();
 #endif  // __HIP_DEVICE_COMPILE__
 }
 

@@ -48,20 +48,19 @@ __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLau
   if (rh >= L * p.h_q) return;         // a whole wavefront: no barrier follows
   const int head = (int)(rh % p.h_q);  // row-major over (row, head)
   const int64_t row = rh / p.h_q;
-  const int64_t range_stride = (int64_t)p.h_q * L;
-  const int64_t base = head * L + row;
+  const int64_t range_stride = L * p.h_q;
   const int quad = lane % QUADS, part = lane / QUADS;
 
   // Lane r holds the log-sum-exp of range r (of 64 at a time).
   float m = -INFINITY;
-  for (int r = lane; r < p.n_ranges; r += 64) m = fmaxf(m, p.ws_lse[r * range_stride + base]);
+  for (int r = lane; r < p.n_ranges; r += 64) m = fmaxf(m, p.ws_lse[r * range_stride + rh]);
   m = wave_max(m);
   float z = 0.f;
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-  const float* o = p.ws_o + base * D + quad * 4;
+  const float* o = p.ws_o + rh * D + quad * 4;
   for (int r0 = 0; r0 < p.n_ranges; r0 += 64) {
     const int n = min(64, p.n_ranges - r0);
-    const float lr = lane < n ? p.ws_lse[(r0 + lane) * range_stride + base] : -INFINITY;
+    const float lr = lane < n ? p.ws_lse[(r0 + lane) * range_stride + rh] : -INFINITY;
     const float w = lr == -INFINITY ? 0.f : expf(lr - m);
     z += w;
     for (int i0 = 0; i0 < n; i0 += kLoadsAhead * PARTS) {
@@ -89,7 +88,7 @@ __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLau
 #pragma unroll
   for (int e = 0; e < 4; ++e) out[e] = (__bf16)(acc[e] * inv);
   *reinterpret_cast<bf16x4*>(p.o + rh * D + quad * 4) = out;
-  if (quad == 0) p.lse[base] = z > 0.f ? m + logf(z) : -INFINITY;
+  if (quad == 0) p.lse[head * L + row] = z > 0.f ? m + logf(z) : -INFINITY;
 }
 
 }  // namespace
