@@ -98,7 +98,7 @@ struct LaunchShape {
 //   * A workgroup costs a tile time per 64-key tile that both of its units
 //     compute and kLoneTile times that for a tile only its longer unit
 //     computes (two waves share its rows' keys, or one wave per SIMD works),
-//     plus kGroupUs of fixed work; one workgroup per compute unit at a time
+//     plus a group time of fixed work; one workgroup per compute unit at a time
 //     (the attention kernel's LDS ring fills a CU).
 //   * The launch time is the makespan of the workgroups in the order the
 //     hardware hands them out: each XCD takes one contiguous run of the
@@ -111,22 +111,47 @@ struct LaunchShape {
 // The constants were measured on MI355X, on launches short enough that the
 // clock holds; only the ranking of candidate plans depends on them.
 constexpr double kTileUs128 = 1.25, kTileUs64 = 0.8;
-constexpr double kGroupUs = 6.0;
+constexpr double kGroupUs128 = 5.0, kGroupUs64 = 3.5;
 constexpr double kMergeBytesPerUs = 5.0e6;
 constexpr double kLaunchUs = 6.0;
+// Rates at which the tiled and the short kernel stream keys and values from
+// HBM (382 MB: 82 and 95 us).  They decide between the two; the weight below 1
+// keeps enough ranges in a plan to reach them (102 MB: 28 us, and 36 us with
+// the fewer ranges that weight 1 chooses).
+constexpr double kTileBytesPerUs = 4.7e6, kShortBytesPerUs = 4.2e6;
+constexpr double kStreamWeight = 0.6;
 constexpr double kLoneTile = 0.65;
 constexpr int kXcds = 8;
 // A workgroup's row groups (see AttnLaunch): single placements are looked at
 // up to this many workgroups per compute unit.
 using mocap::kAdjacent;
 using mocap::kMirrored;
+using mocap::kShort;
 using mocap::kSingle;
 constexpr int64_t kSingleRounds = 2;
+// The short kernel: one round of steps of a workgroup's eight wavefronts (32
+// keys each), fixed work, and how many workgroups per compute unit are looked at.
+constexpr double kStepUs128 = 1.5, kStepUs64 = 0.8;
+constexpr double kShortGroupUs = 2.0;
+constexpr int64_t kShortRounds = 4;
+
+// Workgroups of one KV head and range.
+int workgroups_of_rows(int64_t rows, int pairing) {
+  const int64_t groups = (rows + kUnitRows - 1) / kUnitRows;
+  return (int)(pairing == kShort    ? (rows + kAttnWaveRows - 1) / kAttnWaveRows
+               : pairing == kSingle ? groups
+                                    : (groups + 1) / 2);
+}
 
 // Estimates of `limit` or more may be returned early, from the mean load alone.
 double estimate_launch_us(const LaunchShape& x, int n_ranges, bool own_range, int pairing, double limit) {
   const int group = x.h_q / x.h_kv;
-  const int pairs = mocap::wgs_of_row_groups(x.row_groups, pairing);
+  const int64_t rows = (int64_t)x.chunk_len * group;
+  const int unit_rows = pairing == kShort ? kAttnWaveRows : kUnitRows;
+  const int row_groups = (int)((rows + unit_rows - 1) / unit_rows);
+  const int pairs = workgroups_of_rows(rows, pairing);
+  const double group_us = x.head_dim == 128 ? kGroupUs128 : kGroupUs64;
+  const double step_us = x.head_dim == 128 ? kStepUs128 : kStepUs64;
   const double tile_us = x.head_dim == 128 ? kTileUs128 : kTileUs64;
   const int64_t prefix_tiles = (x.prefix_len + kTileKeys - 1) / kTileKeys;
   const int64_t all_tiles = (x.prefix_len + x.chunk_len + kTileKeys - 1) / kTileKeys;
@@ -135,7 +160,7 @@ double estimate_launch_us(const LaunchShape& x, int n_ranges, bool own_range, in
   // Tiles the unit of row group rg visits among tiles [t0, t1).
   auto unit_tiles = [&](int rg, int64_t t0, int64_t t1) -> int64_t {
     if (rg < 0) return 0;
-    const int64_t tokens = std::min<int64_t>(x.chunk_len, ((int64_t)(rg + 1) * kUnitRows + group - 1) / group);
+    const int64_t tokens = std::min<int64_t>(x.chunk_len, ((int64_t)(rg + 1) * unit_rows + group - 1) / group);
     const int64_t end = (x.prefix_len + tokens + kTileKeys - 1) / kTileKeys;
     return std::max<int64_t>(0, std::min(t1, end) - t0);
   };
@@ -146,11 +171,15 @@ double estimate_launch_us(const LaunchShape& x, int n_ranges, bool own_range, in
     const int64_t t1 = r < parts ? span * (r + 1) / parts : all_tiles;
     for (int q = 0; q < pairs; ++q) {
       // Pair q: row groups q and R-1-q, R-2-2q and R-1-2q, or R-1-q alone.
-      const int top = pairing == kAdjacent ? x.row_groups - 1 - 2 * q : x.row_groups - 1 - q;
-      const int other = pairing == kSingle ? -1 : pairing == kAdjacent ? top - 1 : q < top ? q : -1;
+      const int top = pairing == kAdjacent ? row_groups - 1 - 2 * q : row_groups - 1 - q;
+      const int other = pairing >= kSingle ? -1 : pairing == kAdjacent ? top - 1 : q < top ? q : -1;
       const int64_t a = unit_tiles(top, t0, t1), b = unit_tiles(other, t0, t1);
-      cost.push_back(((double)std::min(a, b) + (double)(std::max(a, b) - std::min(a, b)) * kLoneTile) * tile_us +
-                     kGroupUs);
+      if (pairing == kShort) {
+        cost.push_back((double)((2 * a + kAttnWaves - 1) / kAttnWaves) * step_us + kShortGroupUs);
+      } else {
+        cost.push_back(((double)std::min(a, b) + (double)(std::max(a, b) - std::min(a, b)) * kLoneTile) * tile_us +
+                       group_us);
+      }
     }
   }
   double fixed = kLaunchUs;
@@ -177,16 +206,19 @@ double estimate_launch_us(const LaunchShape& x, int n_ranges, bool own_range, in
       makespan = std::max(makespan, t);
     }
   }
-  return fixed + makespan;
+  const double kv_us = 4.0 * (x.prefix_len + x.chunk_len) * x.h_kv * x.head_dim /
+                       (pairing == kShort ? kShortBytesPerUs : kTileBytesPerUs);
+  return fixed + std::hypot(makespan, kStreamWeight * kv_us);
 }
 
-// MOCAP_PAIRING=mirrored, =adjacent or =single in the environment forces a
+// MOCAP_PAIRING=mirrored, =adjacent, =single or =short in the environment forces a
 // pairing (for tests); -1 = choose.
 int pairing_mode() {
   const char* force = std::getenv("MOCAP_PAIRING");
   if (force && std::strcmp(force, "mirrored") == 0) return kMirrored;
   if (force && std::strcmp(force, "adjacent") == 0) return kAdjacent;
   if (force && std::strcmp(force, "single") == 0) return kSingle;
+  if (force && std::strcmp(force, "short") == 0) return kShort;
   return -1;
 }
 
@@ -200,14 +232,19 @@ double best_pairing_us(const LaunchShape& x, int n_ranges, bool own_range, doubl
   const int mode = pairing_mode();
   int best = mode >= 0 ? mode : kMirrored;
   double best_us = estimate_launch_us(x, n_ranges, own_range, best, limit);
-  if (mode < 0 && x.row_groups > 1) {
-    // Another pairing only when the model expects it to win clearly.  With up
-    // to two row groups the two ways to pair them are the same.
-    for (int pairing : {kAdjacent, kSingle}) {
+  if (mode < 0) {
+    // Another placement only when the model expects it to win clearly.  With
+    // up to two row groups the two ways to pair them are the same, with one
+    // so is single.
+    const int64_t rows = (int64_t)x.chunk_len * (x.h_q / x.h_kv);
+    for (int pairing : {kAdjacent, kSingle, kShort}) {
+      const int64_t wgs = (int64_t)workgroups_of_rows(rows, pairing) * x.h_kv * n_ranges;
       if (pairing == kAdjacent && x.row_groups <= 2) continue;
-      if (pairing == kSingle && (int64_t)x.row_groups * x.h_kv * n_ranges > kSingleRounds * (int64_t)x.slots) continue;
-      const double us = estimate_launch_us(x, n_ranges, own_range, pairing, std::min(limit, best_us * 0.98));
-      if (us < best_us * 0.98) {
+      if (pairing == kSingle && (x.row_groups <= 1 || wgs > kSingleRounds * x.slots)) continue;
+      if (pairing == kShort && wgs > kShortRounds * x.slots) continue;
+      const double bar = best_us * (pairing == kShort ? 0.95 : 0.98);
+      const double us = estimate_launch_us(x, n_ranges, own_range, pairing, std::min(limit, bar));
+      if (us < bar) {
         best_us = us;
         best = pairing;
       }
@@ -274,8 +311,8 @@ int choose_ranges(const LaunchShape& x, int base_wgs, int64_t prefix_tiles, int 
   const int64_t max_n = std::min(all_tiles / kMinRangeTiles, kSplitWgs / base_wgs);
   for (int64_t n = 2; n <= std::min<int64_t>(16, max_n); ++n) consider(n);
   for (int64_t k = 1; k * x.slots <= kSplitWgs; ++k) {
-    for (const int64_t wgs : {(int64_t)base_wgs, (int64_t)x.row_groups * x.h_kv}) {
-      const int64_t n = k * x.slots / wgs;
+    for (const int pairing : {kMirrored, kSingle, kShort}) {
+      const int64_t n = k * x.slots / (workgroups_of_rows((int64_t)x.chunk_len * (x.h_q / x.h_kv), pairing) * (int64_t)x.h_kv);
       if (n > 16 && n <= max_n) consider(n);
     }
   }
@@ -371,7 +408,6 @@ int g_pair_count = 0, g_pair_next = 0;
 
 int choose_pairing(const Plan& plan, int64_t prefix_len, int32_t chunk_len, int32_t h_q, int32_t h_kv,
                     int32_t head_dim, int cus) {
-  if (plan.row_groups <= 1) return kMirrored;
   const PairKey key{prefix_len, chunk_len, h_q, h_kv, head_dim, plan.n_ranges, cus, pairing_mode(),
                     plan.own_range};
   {
@@ -426,7 +462,7 @@ mocap_status enqueue_attention(const mocap_kv_store* kv, const int32_t* block_ta
     if (st != MOCAP_OK) return st;
     p.pairing = choose_pairing(plan, prefix_len, chunk_len, h_q, h_kv, head_dim, cus);
   }
-  p.pairs = mocap::wgs_of_row_groups(plan.row_groups, p.pairing);
+  p.pairs = workgroups_of_rows((int64_t)chunk_len * p.group, p.pairing);
   const int64_t total = (int64_t)p.pairs * h_kv * plan.n_ranges;
   if (total > 0x7fffffff) return MOCAP_ERR_UNSUPPORTED;
   p.block_size = kv->block_size;
@@ -448,7 +484,9 @@ mocap_status enqueue_attention(const mocap_kv_store* kv, const int32_t* block_ta
                                         round_up(rows * (size_t)head_dim * sizeof(float), 256));
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (mocap::launch_chunk_attn(p, head_dim, s) != hipSuccess) return MOCAP_ERR_HIP;
+  const hipError_t launched = p.pairing == kShort ? mocap::launch_chunk_attn_short(p, head_dim, s)
+                                                  : mocap::launch_chunk_attn(p, head_dim, s);
+  if (launched != hipSuccess) return MOCAP_ERR_HIP;
   if (plan.n_ranges > 1) {
     mocap::MergeLaunch m;
     m.ws_o = p.ws_o;

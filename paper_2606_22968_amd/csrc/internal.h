@@ -24,11 +24,10 @@ constexpr int kGroupThreads = 64 * kWavesPerGroup;
 // group 0 alone when the count is odd), or row_groups - 1 - q alone (single).
 // A unit without a group of its own takes half of every tile of the other
 // unit's group.
-enum Pairing { kMirrored = 0, kAdjacent = 1, kSingle = 2 };
-inline int wgs_of_row_groups(int row_groups, int pairing) {
-  return pairing == kSingle ? row_groups : row_groups / 2 + row_groups % 2;
-}
-
+// kShort is the other attention kernel (chunk_attn_short.hip): a workgroup
+// owns one slot of 32 rows and its wavefronts share the slot's keys; `pairs`
+// counts those slots.
+//
 // KV ranges: n_ranges == 1 is the unsplit launch over [0, P + L).  Otherwise
 // the span_tiles tiles of [0, span_end) are cut evenly into span_parts ranges,
 // and a range n_ranges > span_parts is the chunk's own keys [P, P + L): either
@@ -36,6 +35,8 @@ inline int wgs_of_row_groups(int row_groups, int pairing) {
 // chunk's keys are the last range (span_parts == n_ranges - 1).  Tile t holds
 // keys [64 t, 64 t + 64); tiles [remote_begin, remote_end) are read from the
 // second store, every other tile from the first.
+enum Pairing { kMirrored = 0, kAdjacent = 1, kSingle = 2, kShort = 3 };
+
 struct AttnLaunch {
   const uint16_t* q;        // bf16 [L][Hq][D]
   const uint16_t* k_pool;   // bf16 [nb][Hkv][bs][D]
@@ -94,6 +95,7 @@ struct MergeLaunch {
 };
 
 hipError_t launch_chunk_attn(const AttnLaunch& p, int head_dim, hipStream_t stream);
+hipError_t launch_chunk_attn_short(const AttnLaunch& p, int head_dim, hipStream_t stream);
 hipError_t launch_kv_append(const AppendLaunch& p, int head_dim, hipStream_t stream);
 hipError_t launch_lse_merge(const MergeLaunch& p, int head_dim, hipStream_t stream);
 
