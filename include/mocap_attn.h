@@ -172,6 +172,31 @@ mocap_status mocap_chunk_attn(const mocap_kv_store* kv, const int32_t* block_tab
                               void* stream);
 
 /*
+ * mocap_chunk_prefill -- a whole chunk sequence (Section 2.2): for every chunk
+ * in order, mocap_kv_append of its keys and values and mocap_chunk_attn behind
+ * the chunks before it, enqueued by one call.  The results are bitwise those of
+ * the calls made one by one.
+ *
+ *   kv, block_table, n_table  KV store for positions [0, S), S = sum of lengths
+ *   lengths     host, num_chunks chunk lengths (0 is a no-op)
+ *   q, o        device bf16 [S][h_q][head_dim];  k, v  device bf16
+ *               [S][h_kv][head_dim]
+ *   lse         device fp32, one [h_q][L_c] region per chunk, in order, each
+ *               rounded up to a multiple of 4 values
+ *   workspace   large enough for every chunk's plan (the largest
+ *               mocap_chunk_attn_workspace_size)
+ *   other arguments   as in mocap_chunk_attn
+ * Errors: as mocap_kv_append and mocap_chunk_attn, plus INVALID_ARG for a
+ * negative num_chunks or null lengths.  The call stops at the first chunk that
+ * fails; the chunks before it stay enqueued.
+ */
+mocap_status mocap_chunk_prefill(const mocap_kv_store* kv, const int32_t* block_table, int32_t n_table,
+                                 const int32_t* lengths, int32_t num_chunks, const void* q, const void* k,
+                                 const void* v, int32_t h_q, int32_t h_kv, int32_t head_dim, float scale, void* o,
+                                 float* lse, void* workspace, size_t workspace_bytes, int32_t num_splits,
+                                 void* stream);
+
+/*
  * mocap_chunk_attn_two_store -- mocap_chunk_attn for a chunk whose prefix KV
  * lives partly in a second store: the memory-balanced KV reallocation of
  * Section 4.1, where a debtor stage's KV accesses split into a remote portion

@@ -29,6 +29,7 @@ EXPORTED = (
     "mocap_kv_append",
     "mocap_chunk_attn_workspace_size",
     "mocap_chunk_attn",
+    "mocap_chunk_prefill",
     "mocap_chunk_attn_noalloc",
     "mocap_chunk_attn_two_store",
     "mocap_chunk_attn_two_store_workspace_size",
@@ -112,6 +113,12 @@ def load_library():
         ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
         ctypes.c_float, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t,
         ctypes.c_int32, ctypes.c_void_p]
+    lib.mocap_chunk_prefill.restype = st
+    lib.mocap_chunk_prefill.argtypes = [
+        ctypes.POINTER(mocap_kv_store), ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32),
+        ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32,
+        ctypes.c_int32, ctypes.c_float, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t,
+        ctypes.c_int32, ctypes.c_void_p]
     lib.mocap_chunk_attn_noalloc.restype = st
     lib.mocap_chunk_attn_noalloc.argtypes = [
         ctypes.POINTER(mocap_kv_store), ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p,
@@ -179,11 +186,15 @@ def _check(status: int, where: str):
 
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # The current stream's handle without the Stream object around it.
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream
 
 
 def _require(t: torch.Tensor, dtype, name: str, ndim: Optional[int] = None):
+    if isinstance(t, torch.Tensor) and t.dtype == dtype and t.is_cuda and t.is_contiguous() and \
+            (ndim is None or t.dim() == ndim):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -192,8 +203,7 @@ def _require(t: torch.Tensor, dtype, name: str, ndim: Optional[int] = None):
         raise ValueError(f"{name} must be a GPU tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if ndim is not None and t.dim() != ndim:
-        raise ValueError(f"{name} must have {ndim} dimensions, got {tuple(t.shape)}")
+    raise ValueError(f"{name} must have {ndim} dimensions, got {tuple(t.shape)}")
 
 
 class KvStore:
@@ -287,6 +297,35 @@ def mocap_chunk_attn(store: KvStore, block_table: torch.Tensor, q: torch.Tensor,
         int(prefix_len), chunk_len, h_q, store.h_kv, head_dim, float(scale), o.data_ptr(),
         lse.data_ptr(), ws_ptr, ws_bytes, int(num_splits), _stream_handle(stream)),
         "mocap_chunk_attn")
+
+
+def mocap_chunk_prefill(store: KvStore, block_table: torch.Tensor, lengths: Sequence[int], q: torch.Tensor,
+                        k: torch.Tensor, v: torch.Tensor, scale: float, o: torch.Tensor, lse: torch.Tensor,
+                        workspace: Optional[torch.Tensor] = None, num_splits: int = 0, stream=None) -> None:
+    """Every chunk's append and attention.  q, o: bf16 [S][h_q][head_dim]; k, v: bf16 [S][h_kv][head_dim], S at
+    least the sum of the lengths; lse: fp32, flat, one [h_q][L_c] region per chunk, each rounded up to 4 values."""
+    _require(block_table, torch.int32, "block_table", 1)
+    for name, t in (("q", q), ("k", k), ("v", v), ("o", o)):
+        _require(t, torch.bfloat16, name, 3)
+    _require(lse, torch.float32, "lse", 1)
+    total = sum(lengths)
+    h_q, head_dim = q.shape[1:]
+    if min(t.shape[0] for t in (q, k, v, o)) < total or o.shape[1:] != q.shape[1:] or k.shape[1:] != v.shape[1:] or \
+            tuple(k.shape[1:]) != (store.h_kv, store.head_dim):
+        raise ValueError("q/o must be [S][h_q][head_dim] and k/v [S][h_kv][head_dim] of the store")
+    if lse.numel() < sum((h_q * n + 3) // 4 * 4 for n in lengths):
+        raise ValueError("lse is too small for the chunks")
+    ws_ptr, ws_bytes = None, 0
+    if workspace is not None:
+        _require(workspace, workspace.dtype, "workspace")
+        ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
+    _maybe_check(store, block_table, 0, total)
+    desc = store.descriptor()
+    _check(load_library().mocap_chunk_prefill(
+        ctypes.byref(desc), block_table.data_ptr(), block_table.numel(), (ctypes.c_int32 * len(lengths))(*lengths),
+        len(lengths), q.data_ptr(), k.data_ptr(), v.data_ptr(), h_q, store.h_kv, head_dim, float(scale), o.data_ptr(),
+        lse.data_ptr(), ws_ptr, ws_bytes, int(num_splits), _stream_handle(stream)),
+        "mocap_chunk_prefill")
 
 
 def mocap_chunk_attn_noalloc(store: KvStore, block_table: torch.Tensor, q: torch.Tensor, prefix_len: int,

@@ -661,6 +661,34 @@ mocap_status mocap_chunk_attn(const mocap_kv_store* kv, const int32_t* block_tab
                            head_dim, scale, o, lse, workspace, workspace_bytes, stream);
 }
 
+mocap_status mocap_chunk_prefill(const mocap_kv_store* kv, const int32_t* block_table, int32_t n_table,
+                                 const int32_t* lengths, int32_t num_chunks, const void* q, const void* k,
+                                 const void* v, int32_t h_q, int32_t h_kv, int32_t head_dim, float scale, void* o,
+                                 float* lse, void* workspace, size_t workspace_bytes, int32_t num_splits,
+                                 void* stream) {
+  mocap_status st = check_store(kv);
+  if (st != MOCAP_OK) return st;
+  if (num_chunks < 0 || (num_chunks > 0 && lengths == nullptr) || h_q <= 0) return MOCAP_ERR_INVALID_ARG;
+  const int64_t q_row = (int64_t)h_q * head_dim, kv_row = (int64_t)kv->h_kv * kv->head_dim;
+  // Null stays null, for the calls below to refuse.
+  auto row = [](const void* base, int64_t elems) -> const void* {
+    return base ? static_cast<const uint16_t*>(base) + elems : nullptr;
+  };
+  int64_t prefix = 0, lse_at = 0;
+  for (int32_t c = 0; c < num_chunks; ++c) {
+    const int32_t n = lengths[c];
+    st = mocap_kv_append(kv, block_table, n_table, prefix, n, row(k, prefix * kv_row), row(v, prefix * kv_row), stream);
+    if (st != MOCAP_OK) return st;
+    st = mocap_chunk_attn(kv, block_table, n_table, row(q, prefix * q_row), prefix, n, h_q, h_kv, head_dim, scale,
+                          const_cast<void*>(row(o, prefix * q_row)), lse ? lse + lse_at : nullptr, workspace,
+                          workspace_bytes, num_splits, stream);
+    if (st != MOCAP_OK) return st;
+    prefix += n;
+    lse_at += ((int64_t)h_q * n + 3) / 4 * 4;
+  }
+  return MOCAP_OK;
+}
+
 mocap_status mocap_check_block_table(const int32_t* block_table, int32_t n_table, int64_t first_pos,
                                      int64_t end_pos, int32_t block_size, int32_t num_blocks,
                                      int32_t* bad_index_out) {

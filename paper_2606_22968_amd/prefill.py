@@ -71,6 +71,7 @@ class ChunkedPrefill:
             self._lse_off.append(off)
             off += (h_q * n + 3) // 4 * 4
         self._lse_flat = torch.empty(max(off, 4), dtype=torch.float32, device=device)
+        self._planned = (list(self.lengths), list(self.prefixes))
 
     def lse(self, c: int) -> torch.Tensor:
         n = self.lengths[c]
@@ -105,6 +106,24 @@ class ChunkedPrefill:
             binding.mocap_chunk_attn(self.store, self.table, q[p:p + n], p, scale, self.o[p:p + n],
                                      self.lse(c), self.workspace, self.num_splits, stream)
 
+    def _one_call(self, q, k, v) -> bool:
+        """Whether the whole sequence can go to the library in one call: one
+        store, the chunks as planned, nothing of this class replaced, tables not
+        checked call by call, and whole inputs of which every chunk's slice
+        would be accepted (anything else takes, or fails in, the loop)."""
+        if self.remote is not None or binding._check_tables or not self.lengths:
+            return False
+        if type(self) is not ChunkedPrefill or not vars(self).keys().isdisjoint(("append", "attend", "lse")):
+            return False
+        if (self.lengths, self.prefixes) != self._planned:
+            return False
+        for t, heads in ((q, self.h_q), (k, self.h_kv), (v, self.h_kv)):
+            if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous()
+                    and t.dim() == 3 and t.shape[0] >= self.seq_len and t.shape[1] == heads
+                    and t.shape[2] == self.head_dim):
+                return False
+        return True
+
     def run(self, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, scale: float, stream=None,
             events: Optional[list] = None):
         """All chunks in order.  q [S][Hq][d], k/v [S][Hkv][d] bf16 on the device.
@@ -112,6 +131,10 @@ class ChunkedPrefill:
         events, if given, is a list of (start, after_append, end) event triples,
         one per chunk, recorded around each chunk's calls.
         """
+        if events is None and self._one_call(q, k, v):
+            binding.mocap_chunk_prefill(self.store, self.table, self.lengths, q, k, v, scale, self.o, self._lse_flat,
+                                        self.workspace, self.num_splits, stream)
+            return self.o
         for c in range(len(self.lengths)):
             if events is not None:
                 events[c][0].record(stream)

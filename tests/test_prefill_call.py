@@ -1,0 +1,82 @@
+"""mocap_chunk_prefill: a whole chunk sequence in one call gives the bits of the
+calls made one by one, and ChunkedPrefill.run takes it only where the loop would
+accept the same inputs."""
+import ctypes
+
+import pytest
+import torch
+
+from helpers import say
+from paper_2606_22968_amd import binding, synth
+from paper_2606_22968_amd.prefill import ChunkedPrefill
+
+FAKE = 0x10000  # aligned, never dereferenced
+INVALID, UNSUPPORTED = 1, 2
+
+
+def _call(lib, kv="", lengths=(64, 64), n_table=64, num_chunks=None, k=FAKE, h_q=32, block_size=256):
+    store = binding.mocap_kv_store(FAKE, FAKE, 64, block_size, 8, 128)
+    arr = (ctypes.c_int32 * len(lengths))(*lengths) if lengths is not None else None
+    return lib.mocap_chunk_prefill(None if kv is None else ctypes.byref(store), FAKE, n_table, arr,
+                                   len(lengths or ()) if num_chunks is None else num_chunks, FAKE, k, FAKE, h_q, 8,
+                                   128, 0.1, FAKE, FAKE, None, 0, 0, None)
+
+
+@pytest.mark.parametrize("kwargs,expect", [
+    (dict(kv=None), INVALID),
+    (dict(block_size=100), UNSUPPORTED),
+    (dict(lengths=None, num_chunks=2), INVALID),
+    (dict(num_chunks=-1), INVALID),
+    (dict(lengths=(-3, 5)), INVALID),
+    (dict(n_table=0), INVALID),
+    (dict(k=0), INVALID),
+    (dict(k=FAKE + 2), INVALID),
+    (dict(h_q=0), INVALID),
+    (dict(lengths=(), num_chunks=0), 0),
+])
+def test_refused_before_anything_is_enqueued(mocap_lib, kwargs, expect):
+    assert _call(mocap_lib.load_library(), **kwargs) == expect
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("h_q,h_kv,d,lengths,splits", [
+    (8, 8, 64, [256, 256, 1, 77], 0),
+    (6, 3, 128, [5, 0, 130, 700], 0),   # LSE regions off 16 bytes, an empty chunk
+    (8, 2, 128, [300, 200], 3),
+])
+def test_one_call_equals_the_loop(gpu, h_q, h_kv, d, lengths, splits):
+    say(f"[case] one call h_q={h_q} h_kv={h_kv} d={d} lengths={lengths} splits={splits}")
+    S = sum(lengths)
+    q, k, v = (t.cuda() for t in synth.make_qkv(95, S + 3, h_q, h_kv, d))  # more tokens than the chunks use
+    runs = []
+    for events in (None, [[torch.cuda.Event() for _ in range(3)] for _ in lengths]):  # events: the loop
+        r = ChunkedPrefill(h_q, h_kv, d, lengths, block_size=64, num_splits=splits, pool_fill=0.0)
+        r.o.fill_(float("nan"))
+        assert r._one_call(q, k, v)
+        r.run(q, k, v, d ** -0.5, events=events)
+        torch.cuda.synchronize()
+        runs.append(r)
+    one, loop = runs
+    assert torch.equal(one.o.view(torch.int16), loop.o.view(torch.int16))
+    assert torch.equal(one.store.k_pool, loop.store.k_pool) and torch.equal(one.store.v_pool, loop.store.v_pool)
+    for c in range(len(lengths)):
+        assert torch.equal(one.lse(c), loop.lse(c))
+
+
+@pytest.mark.gpu
+def test_inputs_the_loop_refuses_stay_refused(gpu):
+    r = ChunkedPrefill(8, 2, 64, [64, 64], block_size=64)
+    q, k, v = (t.cuda() for t in synth.make_qkv(96, 128, 8, 2, 64))
+    with pytest.raises(ValueError):
+        r.run(q[:100], k, v, 0.1)                       # too few tokens
+    with pytest.raises(TypeError):
+        r.run(q.float(), k, v, 0.1)
+    with pytest.raises(ValueError):
+        r.run(q.transpose(1, 2), k, v, 0.1)             # not contiguous
+    with pytest.raises(ValueError):
+        r.run(q, k.view(128, 1, 128), v.view(128, 1, 128), 0.1)  # other heads
+    with pytest.raises(ValueError):
+        r.run(q, k, v.cpu(), 0.1)
+    with pytest.raises(binding.MocapError) as e:
+        r.run(q, k, v, 0.0)
+    assert e.value.status == INVALID
