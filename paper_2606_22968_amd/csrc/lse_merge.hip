@@ -10,10 +10,12 @@
 // dependent loads, many by HBM (n_ranges (D + 1) 4 bytes read per row), so
 // every load that can be is in flight at once: lane r takes range r's
 // log-sum-exp, the wavefront forms all weights together, and its 64 / (D / 4)
-// parts read the partials of as many ranges at a time, kLoadsAhead deep.
-// Measured, 8B heads, against one thread per 4 outputs that walked the ranges
-// one after the other: 7 rows x 17 ranges 15.4 -> 4.0 us, 137 x 9
-// 10.7 -> 6.3 us, 300 x 17 28.9 -> 19.0 us (8 loads deep: 4.0, 7.3, 20.5).
+// parts read the partials of as many ranges at a time, two batches of loads in
+// flight, the first before the weights are known.  Measured, 8B heads, against
+// one thread per 4 outputs that walked the ranges one after the other: 7 rows
+// x 17 ranges 15.4 -> 4.0 us, 137 x 9 10.7 -> 6.3 us, 300 x 17 28.9 -> 19.0 us
+// with one batch of four loads behind the weights; the second batch and the
+// early start take another 0.6 to 1.9 us off calls with 16 to 128 ranges.
 #include "internal.h"
 
 #include <math.h>
@@ -24,7 +26,12 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kLoadsAhead = 4;  // partials in flight per lane
+// Partials a lane requests at a time.  Up to kFewRows rows the loads' latency
+// counts, above that more loads per lane only crowd the caches.  4 and 8
+// ahead: 16 rows x 128 ranges 37.4 and 35.0 us with their attention, 224 x 32
+// 17.2 and 16.6, 576 x 16 35.6 and 35.8, 4096 x 20 238 and 242.
+constexpr int kLoadsMany = 4, kLoadsFew = 8;
+constexpr int64_t kFewRows = 512;
 
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
@@ -38,7 +45,7 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
-template <int D>
+template <int D, int kLoadsAhead>
 __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLaunch p) {
   constexpr int QUADS = D / 4;         // lanes that hold one partial row
   constexpr int PARTS = 64 / QUADS;    // ranges a wavefront reads at a time
@@ -51,30 +58,46 @@ __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLau
   const int64_t range_stride = L * p.h_q;
   const int quad = lane % QUADS, part = lane / QUADS;
 
-  // Lane r holds the log-sum-exp of range r (of 64 at a time).
-  float m = -INFINITY;
-  for (int r = lane; r < p.n_ranges; r += 64) m = fmaxf(m, p.ws_lse[r * range_stride + rh]);
+  // Ranges are taken 64 at a time: lane r holds the log-sum-exp of range r, and
+  // the partials of the next kLoadsAhead ranges of each part are requested
+  // before those at hand are used, the first ones before any weight is known.
+  const float* o = p.ws_o + rh * D + quad * 4;
+  f32x4 next[kLoadsAhead];
+  auto fetch = [&](int r0, int n, int i0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < kLoadsAhead; ++j)
+      next[j] = *reinterpret_cast<const f32x4*>(o + (r0 + min(i0 + j * PARTS + part, n - 1)) * range_stride * D);
+  };
+  auto load_lse = [&](int r) { return r < p.n_ranges ? p.ws_lse[r * range_stride + rh] : -INFINITY; };
+  float lr = load_lse(lane);
+  fetch(0, min(64, p.n_ranges), 0);
+  float m = lr;
+  for (int r = lane + 64; r < p.n_ranges; r += 64) m = fmaxf(m, load_lse(r));
   m = wave_max(m);
   float z = 0.f;
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-  const float* o = p.ws_o + rh * D + quad * 4;
   for (int r0 = 0; r0 < p.n_ranges; r0 += 64) {
     const int n = min(64, p.n_ranges - r0);
-    const float lr = lane < n ? p.ws_lse[(r0 + lane) * range_stride + rh] : -INFINITY;
+    if (r0 > 0) {
+      lr = load_lse(r0 + lane);
+      fetch(r0, n, 0);
+    }
     const float w = lr == -INFINITY ? 0.f : expf(lr - m);
     z += w;
     for (int i0 = 0; i0 < n; i0 += kLoadsAhead * PARTS) {
       f32x4 v[kLoadsAhead];
-      float wi[kLoadsAhead];
+#pragma unroll
+      for (int j = 0; j < kLoadsAhead; ++j) v[j] = next[j];
+      if (i0 + kLoadsAhead * PARTS < n) fetch(r0, n, i0 + kLoadsAhead * PARTS);
 #pragma unroll
       for (int j = 0; j < kLoadsAhead; ++j) {
         const int i = i0 + j * PARTS + part;
-        wi[j] = __shfl(w, i & 63);  // 0 for i in [n, 64)
-        if (i >= n) wi[j] = 0.f;
-        v[j] = wi[j] != 0.f ? *reinterpret_cast<const f32x4*>(o + (r0 + i) * range_stride * D) : f32x4{};
-      }
+        float wi = __shfl(w, i & 63);  // every lane: the source lane takes part
+        if (i >= n) wi = 0.f;
+        // A range that no key of the row falls into has weight 0 and is left out.
 #pragma unroll
-      for (int j = 0; j < kLoadsAhead; ++j) acc += wi[j] * v[j];
+        for (int e = 0; e < 4; ++e) acc[e] += wi * (wi != 0.f ? v[j][e] : 0.f);
+      }
     }
   }
   z = wave_sum(z);
@@ -96,10 +119,19 @@ __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLau
 hipError_t launch_lse_merge(const MergeLaunch& p, int head_dim, hipStream_t stream) {
   const int64_t rows = (int64_t)p.chunk_len * p.h_q;
   const dim3 grid((unsigned)((rows + kWavesPerGroup - 1) / kWavesPerGroup)), block(kGroupThreads);
+  const bool few = rows <= kFewRows;
   if (head_dim == 128) {
-    hipLaunchKernelGGL(lse_merge_kernel<128>, grid, block, 0, stream, p);
+    if (few) {
+      hipLaunchKernelGGL((lse_merge_kernel<128, kLoadsFew>), grid, block, 0, stream, p);
+    } else {
+      hipLaunchKernelGGL((lse_merge_kernel<128, kLoadsMany>), grid, block, 0, stream, p);
+    }
   } else {
-    hipLaunchKernelGGL(lse_merge_kernel<64>, grid, block, 0, stream, p);
+    if (few) {
+      hipLaunchKernelGGL((lse_merge_kernel<64, kLoadsFew>), grid, block, 0, stream, p);
+    } else {
+      hipLaunchKernelGGL((lse_merge_kernel<64, kLoadsMany>), grid, block, 0, stream, p);
+    }
   }
   return hipGetLastError();
 }

@@ -18,3 +18,11 @@ def test_merge_any_range_count(gpu, oracle_lib, splits, h_q, h_kv, d):
     runner = run_gpu(q, k, v, lengths, scale, block_size=64, num_splits=splits)
     assert runner.splits[1] == min(splits, 131)
     check_chunks(oracle_lib, runner, q, k, v, scale, rows_of=lambda c, n: [0, 1, 4], label=f"splits={splits}")
+
+
+@pytest.mark.parametrize("length", [128, 129])
+def test_merge_few_and_many_rows(gpu, oracle_lib, length):
+    """512 and 516 (token, head) rows: both sides of the loads-ahead rule."""
+    q, k, v = synth.make_qkv(92, 2048 + length, 4, 2, 64)
+    runner = run_gpu(q, k, v, [2048, length], 0.125, block_size=64, num_splits=21)
+    check_chunks(oracle_lib, runner, q, k, v, 0.125, rows_of=lambda c, n: [0, 1, 63, n - 1], label=f"rows={4 * length}")
