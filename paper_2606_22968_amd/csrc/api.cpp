@@ -13,7 +13,6 @@
 #include <cstring>
 #include <functional>
 #include <mutex>
-#include <queue>
 #include <utility>
 #include <vector>
 
@@ -195,14 +194,26 @@ double estimate_launch_us(const LaunchShape& x, int n_ranges, bool own_range, in
   if (fixed + mean >= limit) return fixed + mean;
   double makespan = 0.0;
   int64_t next = 0;
+  const int64_t size = (int64_t)cost.size();
+  std::pair<int64_t, int64_t> seen[kXcds];  // (first workgroup of its KV head, count) of the XCDs so far
+  std::vector<double> busy_until;
   for (int xcd = 0; xcd < kXcds; ++xcd) {
-    const int64_t end = next + total_wgs / kXcds + (xcd < total_wgs % kXcds ? 1 : 0);
-    std::priority_queue<double, std::vector<double>, std::greater<double>> load;
-    for (int i = 0; i < xcd_slots; ++i) load.push(0.0);
-    for (; next < end; ++next) {
-      const double t = load.top() + cost[(size_t)(next % (int64_t)cost.size())];
-      load.pop();
-      load.push(t);
+    const int64_t begin = next, count = total_wgs / kXcds + (xcd < total_wgs % kXcds ? 1 : 0);
+    next += count;
+    seen[xcd] = {begin % size, count};
+    if (std::find(seen, seen + xcd, seen[xcd]) != seen + xcd) continue;  // runs the same workgroups
+    busy_until.clear();
+    for (int64_t i = begin; i < next; ++i) {
+      double t = cost[(size_t)(i % size)];
+      if ((int)busy_until.size() == xcd_slots) {
+        if (i - begin == xcd_slots) std::make_heap(busy_until.begin(), busy_until.end(), std::greater<double>());
+        std::pop_heap(busy_until.begin(), busy_until.end(), std::greater<double>());
+        t += busy_until.back();
+        busy_until.back() = t;
+        std::push_heap(busy_until.begin(), busy_until.end(), std::greater<double>());
+      } else {
+        busy_until.push_back(t);
+      }
       makespan = std::max(makespan, t);
     }
   }
@@ -274,8 +285,11 @@ PlanKey g_plan_keys[kPlanCache];
 int g_plan_values[kPlanCache];
 int g_plan_count = 0, g_plan_next = 0;
 
-// Most workgroups of a split launch, and fewest tiles of a range.
-constexpr int64_t kSplitWgs = 4096;
+// Most workgroups of a split launch (of few ranges, which even out the long
+// chunks of a prompt, or of many, which only cost planning time beyond that),
+// and fewest tiles of a range.
+constexpr int64_t kSplitWgsFew = 4096, kSplitWgsMany = 2048;
+constexpr int64_t kFewRanges = 8;
 constexpr int64_t kMinRangeTiles = 4;
 
 // Number of KV ranges to use.  A requested count is clamped to what the
@@ -308,9 +322,10 @@ int choose_ranges(const LaunchShape& x, int base_wgs, int64_t prefix_tiles, int 
     }
   };
   const int64_t all_tiles = (x.prefix_len + x.chunk_len + kTileKeys - 1) / kTileKeys;
-  const int64_t max_n = std::min(all_tiles / kMinRangeTiles, kSplitWgs / base_wgs);
+  const int64_t max_n = std::min(all_tiles / kMinRangeTiles,
+                                 std::max(std::min(kFewRanges, kSplitWgsFew / base_wgs), kSplitWgsMany / base_wgs));
   for (int64_t n = 2; n <= std::min<int64_t>(16, max_n); ++n) consider(n);
-  for (int64_t k = 1; k * x.slots <= kSplitWgs; ++k) {
+  for (int64_t k = 1; k * x.slots <= kSplitWgsMany; ++k) {
     for (const int pairing : {kMirrored, kSingle, kShort}) {
       const int64_t n = k * x.slots / (workgroups_of_rows((int64_t)x.chunk_len * (x.h_q / x.h_kv), pairing) * (int64_t)x.h_kv);
       if (n > 16 && n <= max_n) consider(n);
