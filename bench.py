@@ -36,6 +36,7 @@ Usage: python bench.py [--steps K] [--warmup W] [--workload NAME] [--no-cpu-base
 import argparse
 import json
 import os
+import re
 import statistics
 import sys
 import time
@@ -161,7 +162,7 @@ def summarize_trace(path, workload, steps):
     w = synth.WORKLOADS[workload]
     lengths = binding.mocap_chunk_plan(w.seq_len, w.num_chunks, w.align, balanced=(w.chunking == "balanced"))
     rows = list(csv.DictReader(open(path)))
-    attn = [r for r in rows if "chunk_attn_kernel" in r["Kernel_Name"]]
+    attn = [r for r in rows if re.search(r"chunk_attn_(short_)?kernel", r["Kernel_Name"])]
     n = steps * len(lengths)
     if len(attn) < n:
         raise SystemExit(f"{path}: {len(attn)} attention launches, fewer than {steps} steps x {len(lengths)}")

@@ -51,3 +51,11 @@ def test_attention_two_waves_per_simd(tmp_path):
     for name, r in attn.items():
         assert r["Occupancy [waves/SIMD]"] >= 2, f"{name}: {r}"
         assert r["VGPRs"] + r.get("AGPRs", 0) <= 256, f"{name}: {r}"
+
+
+def test_short_attention_kernel_registers(tmp_path):
+    report = resource_report("chunk_attn_short.hip", str(tmp_path))
+    assert len(report) == 4, sorted(report)  # head_dim 64/128, one or two stores
+    for name, r in report.items():
+        assert r.get("VGPRs Spill", 0) == 0 and r.get("ScratchSize [bytes/lane]", 0) == 0, f"{name}: {r}"
+        assert r["Occupancy [waves/SIMD]"] >= 2, f"{name}: {r}"
