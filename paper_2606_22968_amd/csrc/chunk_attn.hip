@@ -657,7 +657,8 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_kernel(const AttnL
     if (r.token < L) {
       const int head = head0 + r.head;
       const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-      const float row_lse = f_tot > 0.f ? (m_run + log2f(f_tot)) * kLn2 : -INFINITY;
+      // A NaN sum gives a NaN O and log-sum-exp; 0 is a row without a visible key.
+      const float row_lse = f_tot == 0.f ? -INFINITY : (m_run + log2f(f_tot)) * kLn2;
       if (!split) {
         uint16_t* orow = p.o + ((int64_t)r.token * p.h_q + head) * D;
 #pragma unroll

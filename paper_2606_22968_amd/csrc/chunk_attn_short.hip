@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_short_kernel(const
   }
 
   // Partials of the wavefronts meet in LDS.  A wavefront without steps leaves
-  // m = -inf, so its weight is 0 and its O is not read.
+  // a sum of 0, so its weight is 0 and its O is not read.
   const float l_tot = lane_pair_sum(l_run), f_tot = lane_pair_sum(f_run);
   if (half == 0) {
     part_m[wave][l32] = m_run;
@@ -275,21 +275,26 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_short_kernel(const
   __syncthreads();
 
   // Wavefront w sums the pieces (md, j) = w, w + 8, ... of all partials; the
-  // row of a lane stays the same.
+  // row of a lane stays the same.  A partial counts if its sum is not 0: a NaN
+  // score leaves m = -inf (fmaxf drops it) and a NaN sum, which has to reach
+  // O and the log-sum-exp.
   float m = -INFINITY;
 #pragma unroll
   for (int w = 0; w < kAttnWaves; ++w) m = fmaxf(m, part_m[w][l32]);
   float weight[kAttnWaves], l = 0.f, f = 0.f;
+  uint32_t counts = 0;
 #pragma unroll
   for (int w = 0; w < kAttnWaves; ++w) {
-    const float m_w = part_m[w][l32];
-    weight[w] = m_w == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_w - m);
-    l += part_l[w][l32] * weight[w];
+    const float l_w = part_l[w][l32];
+    const bool any = l_w != 0.f;
+    counts |= any ? 1u << w : 0u;
+    weight[w] = any ? __builtin_amdgcn_exp2f(part_m[w][l32] - m) : 0.f;
+    l += l_w * weight[w];
     f += part_f[w][l32] * weight[w];
   }
   if (token >= L) return;
   const float inv = l > 0.f ? 1.f / l : 0.f;
-  const float row_lse = f > 0.f ? (m + log2f(f)) * kLn2 : -INFINITY;
+  const float row_lse = f == 0.f ? -INFINITY : (m + log2f(f)) * kLn2;
   const bool split = p.n_ranges > 1;
   const int64_t out_row = (int64_t)token * p.h_q + head;
   const int64_t ws_row = (int64_t)range * L * p.h_q + out_row;
@@ -299,10 +304,9 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_short_kernel(const
 #pragma unroll
     for (int w = 0; w < kAttnWaves; ++w) {
       const f32x4 o_w = reinterpret_cast<const f32x4*>(ring[w])[piece * 64 + lane];
-      // A wavefront without a visible key of this row (or without steps, whose
-      // ring holds anything) has weight 0.
+      // The ring of a wavefront without steps holds anything.
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] += weight[w] * (weight[w] != 0.f ? o_w[e] : 0.f);
+      for (int e = 0; e < 4; ++e) o[e] += weight[w] * ((counts >> w & 1u) != 0 ? o_w[e] : 0.f);
     }
     o *= inv;
     const int dim = piece * 8 + half * 4;  // (md, j) covers dims md * 32 + j * 8

@@ -82,8 +82,11 @@ __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLau
       lr = load_lse(r0 + lane);
       fetch(r0, n, 0);
     }
-    const float w = lr == -INFINITY ? 0.f : expf(lr - m);
-    z += w;
+    // A range that no key of the row falls into (-inf) is left out, whatever
+    // its O holds; a NaN reaches the result.
+    const bool has_keys = lr != -INFINITY;
+    const float w = has_keys ? expf(lr - m) : -1.f;
+    z += has_keys ? w : 0.f;
     for (int i0 = 0; i0 < n; i0 += kLoadsAhead * PARTS) {
       f32x4 v[kLoadsAhead];
 #pragma unroll
@@ -93,10 +96,10 @@ __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLau
       for (int j = 0; j < kLoadsAhead; ++j) {
         const int i = i0 + j * PARTS + part;
         float wi = __shfl(w, i & 63);  // every lane: the source lane takes part
-        if (i >= n) wi = 0.f;
-        // A range that no key of the row falls into has weight 0 and is left out.
+        const bool used = i < n && !(wi < 0.f);
+        wi = used ? wi : 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] += wi * (wi != 0.f ? v[j][e] : 0.f);
+        for (int e = 0; e < 4; ++e) acc[e] += wi * (used ? v[j][e] : 0.f);
       }
     }
   }
@@ -111,7 +114,7 @@ __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLau
 #pragma unroll
   for (int e = 0; e < 4; ++e) out[e] = (__bf16)(acc[e] * inv);
   *reinterpret_cast<bf16x4*>(p.o + rh * D + quad * 4) = out;
-  if (quad == 0) p.lse[head * L + row] = z > 0.f ? m + logf(z) : -INFINITY;
+  if (quad == 0) p.lse[head * L + row] = z == 0.f ? -INFINITY : m + logf(z);
 }
 
 }  // namespace
