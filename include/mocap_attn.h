@@ -187,8 +187,8 @@ mocap_status mocap_chunk_attn(const mocap_kv_store* kv, const int32_t* block_tab
  *               mocap_chunk_attn_workspace_size)
  *   other arguments   as in mocap_chunk_attn
  * Errors: as mocap_kv_append and mocap_chunk_attn, plus INVALID_ARG for a
- * negative num_chunks or null lengths.  The call stops at the first chunk that
- * fails; the chunks before it stay enqueued.
+ * negative num_chunks or null lengths.  Every chunk is checked before the first
+ * one is enqueued, so on any status but MOCAP_ERR_HIP nothing is written.
  */
 mocap_status mocap_chunk_prefill(const mocap_kv_store* kv, const int32_t* block_table, int32_t n_table,
                                  const int32_t* lengths, int32_t num_chunks, const void* q, const void* k,

@@ -308,6 +308,8 @@ def mocap_chunk_prefill(store: KvStore, block_table: torch.Tensor, lengths: Sequ
     for name, t in (("q", q), ("k", k), ("v", v), ("o", o)):
         _require(t, torch.bfloat16, name, 3)
     _require(lse, torch.float32, "lse", 1)
+    if min(lengths, default=0) < 0:
+        raise ValueError("chunk lengths must not be negative")
     total = sum(lengths)
     h_q, head_dim = q.shape[1:]
     if min(t.shape[0] for t in (q, k, v, o)) < total or o.shape[1:] != q.shape[1:] or k.shape[1:] != v.shape[1:] or \

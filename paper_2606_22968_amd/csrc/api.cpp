@@ -12,7 +12,9 @@
 #include <cstdlib>
 #include <cstring>
 #include <functional>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <utility>
 #include <vector>
 
@@ -441,20 +443,28 @@ int choose_pairing(const Plan& plan, int64_t prefix_len, int32_t chunk_len, int3
   return pairing;
 }
 
-// Launches the attention kernel (and the merge when the plan is split).
-// Arguments have been validated; remote_kv is used only for the plan's
-// second-store ranges.
-mocap_status enqueue_attention(const mocap_kv_store* kv, const int32_t* block_table, const mocap_kv_store* remote_kv,
+// The launches of one chunk's attention: the attention kernel and, when the
+// plan is split, the merge.
+struct Prepared {
+  mocap::AttnLaunch attn;
+  mocap::MergeLaunch merge;
+  int32_t head_dim;
+};
+
+// Makes the launch descriptions; nothing is enqueued.  Arguments have been
+// validated; remote_kv is used only for the plan's second-store ranges.
+mocap_status prepare_attention(const mocap_kv_store* kv, const int32_t* block_table, const mocap_kv_store* remote_kv,
                                const int32_t* remote_table, const Plan& plan, const void* q, int64_t prefix_len,
                                int32_t chunk_len, int32_t h_q, int32_t h_kv, int32_t head_dim, float scale,
-                               void* o, float* lse, void* workspace, size_t workspace_bytes, void* stream) {
+                               void* o, float* lse, void* workspace, size_t workspace_bytes, Prepared* out) {
   if (plan.units * plan.n_ranges > 0x7fffffff) return MOCAP_ERR_UNSUPPORTED;
   if (plan.n_ranges > 1) {
     if (workspace == nullptr || !aligned16(workspace) || workspace_bytes < plan.ws_bytes)
       return MOCAP_ERR_WORKSPACE;
   }
 
-  mocap::AttnLaunch p;
+  out->head_dim = head_dim;
+  mocap::AttnLaunch& p = out->attn;
   p.q = static_cast<const uint16_t*>(q);
   p.k_pool = static_cast<const uint16_t*>(kv->k_pool);
   p.v_pool = static_cast<const uint16_t*>(kv->v_pool);
@@ -498,21 +508,65 @@ mocap_status enqueue_attention(const mocap_kv_store* kv, const int32_t* block_ta
     p.ws_lse = reinterpret_cast<float*>(static_cast<char*>(workspace) +
                                         round_up(rows * (size_t)head_dim * sizeof(float), 256));
   }
+  mocap::MergeLaunch& m = out->merge;
+  m.ws_o = p.ws_o;
+  m.ws_lse = p.ws_lse;
+  m.o = p.o;
+  m.lse = lse;
+  m.chunk_len = chunk_len;
+  m.h_q = h_q;
+  m.n_ranges = plan.n_ranges;
+  return MOCAP_OK;
+}
+
+mocap_status launch_attention(const Prepared& x, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const hipError_t launched = p.pairing == kShort ? mocap::launch_chunk_attn_short(p, head_dim, s)
-                                                  : mocap::launch_chunk_attn(p, head_dim, s);
+  const hipError_t launched = x.attn.pairing == kShort ? mocap::launch_chunk_attn_short(x.attn, x.head_dim, s)
+                                                       : mocap::launch_chunk_attn(x.attn, x.head_dim, s);
   if (launched != hipSuccess) return MOCAP_ERR_HIP;
-  if (plan.n_ranges > 1) {
-    mocap::MergeLaunch m;
-    m.ws_o = p.ws_o;
-    m.ws_lse = p.ws_lse;
-    m.o = p.o;
-    m.lse = lse;
-    m.chunk_len = chunk_len;
-    m.h_q = h_q;
-    m.n_ranges = plan.n_ranges;
-    if (mocap::launch_lse_merge(m, head_dim, s) != hipSuccess) return MOCAP_ERR_HIP;
-  }
+  if (x.merge.n_ranges > 1 && mocap::launch_lse_merge(x.merge, x.head_dim, s) != hipSuccess) return MOCAP_ERR_HIP;
+  return MOCAP_OK;
+}
+
+mocap_status enqueue_attention(const mocap_kv_store* kv, const int32_t* block_table, const mocap_kv_store* remote_kv,
+                               const int32_t* remote_table, const Plan& plan, const void* q, int64_t prefix_len,
+                               int32_t chunk_len, int32_t h_q, int32_t h_kv, int32_t head_dim, float scale,
+                               void* o, float* lse, void* workspace, size_t workspace_bytes, void* stream) {
+  Prepared x;
+  const mocap_status st = prepare_attention(kv, block_table, remote_kv, remote_table, plan, q, prefix_len, chunk_len,
+                                            h_q, h_kv, head_dim, scale, o, lse, workspace, workspace_bytes, &x);
+  return st == MOCAP_OK ? launch_attention(x, stream) : st;
+}
+
+// Checks of mocap_kv_append.
+mocap_status check_append_args(const mocap_kv_store* kv, const int32_t* block_table, int32_t n_table,
+                               int64_t start_pos, int32_t chunk_len, const void* k_chunk, const void* v_chunk) {
+  mocap_status st = check_store(kv);
+  if (st != MOCAP_OK) return st;
+  st = check_positions(kv, n_table, start_pos, chunk_len);
+  if (st != MOCAP_OK) return st;
+  if (chunk_len == 0) return MOCAP_OK;
+  if (!kv->k_pool || !kv->v_pool || !block_table || !k_chunk || !v_chunk) return MOCAP_ERR_INVALID_ARG;
+  if (!aligned16(kv->k_pool) || !aligned16(kv->v_pool) || !aligned16(block_table) ||
+      !aligned16(k_chunk) || !aligned16(v_chunk))
+    return MOCAP_ERR_INVALID_ARG;
+  return MOCAP_OK;
+}
+
+mocap_status launch_append(const mocap_kv_store* kv, const int32_t* block_table, int64_t start_pos, int32_t chunk_len,
+                           const void* k_chunk, const void* v_chunk, void* stream) {
+  mocap::AppendLaunch p;
+  p.k_chunk = static_cast<const uint16_t*>(k_chunk);
+  p.v_chunk = static_cast<const uint16_t*>(v_chunk);
+  p.k_pool = static_cast<uint16_t*>(kv->k_pool);
+  p.v_pool = static_cast<uint16_t*>(kv->v_pool);
+  p.table = block_table;
+  p.start_pos = start_pos;
+  p.chunk_len = chunk_len;
+  p.h_kv = kv->h_kv;
+  p.block_size = kv->block_size;
+  if (mocap::launch_kv_append(p, kv->head_dim, static_cast<hipStream_t>(stream)) != hipSuccess)
+    return MOCAP_ERR_HIP;
   return MOCAP_OK;
 }
 
@@ -613,30 +667,10 @@ const char* mocap_status_string(mocap_status status) {
 mocap_status mocap_kv_append(const mocap_kv_store* kv, const int32_t* block_table, int32_t n_table,
                              int64_t start_pos, int32_t chunk_len, const void* k_chunk,
                              const void* v_chunk, void* stream) {
-  mocap_status st = check_store(kv);
-  if (st != MOCAP_OK) return st;
-  st = check_positions(kv, n_table, start_pos, chunk_len);
-  if (st != MOCAP_OK) return st;
-  if (chunk_len == 0) return MOCAP_OK;
-  if (!kv->k_pool || !kv->v_pool || !block_table || !k_chunk || !v_chunk) return MOCAP_ERR_INVALID_ARG;
-  if (!aligned16(kv->k_pool) || !aligned16(kv->v_pool) || !aligned16(block_table) ||
-      !aligned16(k_chunk) || !aligned16(v_chunk))
-    return MOCAP_ERR_INVALID_ARG;
+  const mocap_status st = check_append_args(kv, block_table, n_table, start_pos, chunk_len, k_chunk, v_chunk);
+  if (st != MOCAP_OK || chunk_len == 0) return st;
   MOCAP_DEBUG_CHECK(block_table, start_pos, start_pos + chunk_len, kv);
-
-  mocap::AppendLaunch p;
-  p.k_chunk = static_cast<const uint16_t*>(k_chunk);
-  p.v_chunk = static_cast<const uint16_t*>(v_chunk);
-  p.k_pool = static_cast<uint16_t*>(kv->k_pool);
-  p.v_pool = static_cast<uint16_t*>(kv->v_pool);
-  p.table = block_table;
-  p.start_pos = start_pos;
-  p.chunk_len = chunk_len;
-  p.h_kv = kv->h_kv;
-  p.block_size = kv->block_size;
-  if (mocap::launch_kv_append(p, kv->head_dim, static_cast<hipStream_t>(stream)) != hipSuccess)
-    return MOCAP_ERR_HIP;
-  return MOCAP_OK;
+  return launch_append(kv, block_table, start_pos, chunk_len, k_chunk, v_chunk, stream);
 }
 
 mocap_status mocap_chunk_attn_workspace_size(int64_t prefix_len, int32_t chunk_len, int32_t h_q,
@@ -685,21 +719,43 @@ mocap_status mocap_chunk_prefill(const mocap_kv_store* kv, const int32_t* block_
   if (st != MOCAP_OK) return st;
   if (num_chunks < 0 || (num_chunks > 0 && lengths == nullptr) || h_q <= 0) return MOCAP_ERR_INVALID_ARG;
   const int64_t q_row = (int64_t)h_q * head_dim, kv_row = (int64_t)kv->h_kv * kv->head_dim;
-  // Null stays null, for the calls below to refuse.
+  // Null stays null, for the checks to refuse.
   auto row = [](const void* base, int64_t elems) -> const void* {
     return base ? static_cast<const uint16_t*>(base) + elems : nullptr;
   };
+  int32_t used = 0;  // chunks that are not empty
+  for (int32_t c = 0; c < num_chunks; ++c) used += lengths[c] != 0;
+  std::unique_ptr<Prepared[]> prepared(new (std::nothrow) Prepared[used]);
+  if (!prepared) return MOCAP_ERR_UNSUPPORTED;
+  // Every chunk is checked and prepared before the first one is enqueued.
   int64_t prefix = 0, lse_at = 0;
+  Prepared* x = prepared.get();
   for (int32_t c = 0; c < num_chunks; ++c) {
     const int32_t n = lengths[c];
-    st = mocap_kv_append(kv, block_table, n_table, prefix, n, row(k, prefix * kv_row), row(v, prefix * kv_row), stream);
+    const void* q_c = row(q, prefix * q_row);
+    void* o_c = const_cast<void*>(row(o, prefix * q_row));
+    float* lse_c = lse ? lse + lse_at : nullptr;
+    st = check_append_args(kv, block_table, n_table, prefix, n, row(k, prefix * kv_row), row(v, prefix * kv_row));
     if (st != MOCAP_OK) return st;
-    st = mocap_chunk_attn(kv, block_table, n_table, row(q, prefix * q_row), prefix, n, h_q, h_kv, head_dim, scale,
-                          const_cast<void*>(row(o, prefix * q_row)), lse ? lse + lse_at : nullptr, workspace,
-                          workspace_bytes, num_splits, stream);
+    st = check_attn_args(kv, block_table, n_table, q_c, prefix, n, h_q, h_kv, head_dim, scale, o_c, lse_c, num_splits);
+    if (st != MOCAP_OK) return st;
+    if (n == 0) continue;
+    Plan plan;
+    st = make_plan(prefix, n, h_q, h_kv, head_dim, num_splits, &plan);
+    if (st != MOCAP_OK) return st;
+    st = prepare_attention(kv, block_table, nullptr, nullptr, plan, q_c, prefix, n, h_q, h_kv, head_dim, scale, o_c,
+                           lse_c, workspace, workspace_bytes, x++);
     if (st != MOCAP_OK) return st;
     prefix += n;
     lse_at += ((int64_t)h_q * n + 3) / 4 * 4;
+  }
+  MOCAP_DEBUG_CHECK(block_table, 0, prefix, kv);
+  for (const Prepared* y = prepared.get(); y < x; ++y) {
+    const int64_t at = y->attn.prefix_len * kv_row;
+    st = launch_append(kv, block_table, y->attn.prefix_len, y->attn.chunk_len, row(k, at), row(v, at), stream);
+    if (st != MOCAP_OK) return st;
+    st = launch_attention(*y, stream);
+    if (st != MOCAP_OK) return st;
   }
   return MOCAP_OK;
 }

@@ -48,3 +48,24 @@ def gpu(mocap_lib):
     name = torch.cuda.get_device_properties(0).gcnArchName
     print(f"[gpu] device 0: {torch.cuda.get_device_name(0)} ({name})", flush=True)
     return torch.device("cuda:0")
+
+
+@pytest.fixture(scope="session")
+def host_lib(mocap_lib, tmp_path_factory):
+    """The library's host side with recorded launches (host_record.cpp): what a
+    call enqueues on a device of 256 compute units, without a GPU."""
+    import ctypes
+    import subprocess
+
+    from paper_2606_22968_amd import build
+    lib = str(tmp_path_factory.mktemp("host") / "libhost_record.so")
+    sources = [os.path.join(build.CSRC, f) for f in ("api.cpp", "plan.cpp", "lse_merge.hip")]
+    sources.append(os.path.join(ROOT, "tests", "host_record.cpp"))
+    cmd = [build.HIPCC, *build.FLAGS, "-x", "hip", *sources, "-shared", "-Wl,-Bsymbolic", "-o", lib]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    host = ctypes.CDLL(lib)
+    for name in mocap_lib.EXPORTED:
+        f, real = getattr(host, name), getattr(mocap_lib.load_library(), name)
+        f.restype, f.argtypes = real.restype, real.argtypes
+    return host

@@ -11,18 +11,19 @@ from paper_2606_22968_amd import binding, synth
 from paper_2606_22968_amd.prefill import ChunkedPrefill
 
 FAKE = 0x10000  # aligned, never dereferenced
-INVALID, UNSUPPORTED = 1, 2
+INVALID, UNSUPPORTED, WORKSPACE = 1, 2, 3
 
 
-def _call(lib, kv="", lengths=(64, 64), n_table=64, num_chunks=None, k=FAKE, h_q=32, block_size=256):
+def _call(lib, kv="", lengths=(64, 64), n_table=64, num_chunks=None, k=FAKE, h_q=32, h_kv=8, block_size=256,
+          head_dim=128, scale=0.1, o=FAKE, lse=FAKE, ws=None, ws_bytes=0, num_splits=0):
     store = binding.mocap_kv_store(FAKE, FAKE, 64, block_size, 8, 128)
     arr = (ctypes.c_int32 * len(lengths))(*lengths) if lengths is not None else None
     return lib.mocap_chunk_prefill(None if kv is None else ctypes.byref(store), FAKE, n_table, arr,
-                                   len(lengths or ()) if num_chunks is None else num_chunks, FAKE, k, FAKE, h_q, 8,
-                                   128, 0.1, FAKE, FAKE, None, 0, 0, None)
+                                   len(lengths or ()) if num_chunks is None else num_chunks, FAKE, k, FAKE, h_q, h_kv,
+                                   head_dim, scale, o, lse, ws, ws_bytes, num_splits, None)
 
 
-@pytest.mark.parametrize("kwargs,expect", [
+REFUSED = [
     (dict(kv=None), INVALID),
     (dict(block_size=100), UNSUPPORTED),
     (dict(lengths=None, num_chunks=2), INVALID),
@@ -32,10 +33,45 @@ def _call(lib, kv="", lengths=(64, 64), n_table=64, num_chunks=None, k=FAKE, h_q
     (dict(k=0), INVALID),
     (dict(k=FAKE + 2), INVALID),
     (dict(h_q=0), INVALID),
+    # Refused by the attention, or behind a chunk that is in order.
+    (dict(scale=0.0), INVALID),
+    (dict(scale=float("nan")), INVALID),
+    (dict(h_q=12), INVALID),
+    (dict(h_kv=4), INVALID),
+    (dict(head_dim=64), INVALID),
+    (dict(head_dim=256), INVALID),
+    (dict(o=0), INVALID),
+    (dict(lse=0), INVALID),
+    (dict(lse=FAKE + 4), INVALID),
+    (dict(num_splits=-1), INVALID),
+    (dict(num_splits=2), WORKSPACE),
+    (dict(num_splits=2, ws=FAKE, ws_bytes=1024), WORKSPACE),
+    (dict(num_splits=2, ws=FAKE + 8, ws_bytes=1 << 30), WORKSPACE),
+    (dict(lengths=(200, -100)), INVALID),
+    (dict(lengths=(64, 0, 64, 64 * 256)), INVALID),
+    (dict(lengths=(64, 2**31 - 1)), INVALID),
+    (dict(lengths=(64,) * 4, n_table=1, block_size=64), INVALID),
+]
+
+
+@pytest.mark.parametrize("kwargs,expect", REFUSED)
+def test_refused_before_anything_is_enqueued(host_lib, kwargs, expect):
+    before = host_lib.record_launches()
+    assert _call(host_lib, **kwargs) == expect
+    assert host_lib.record_launches() == before
+
+
+@pytest.mark.parametrize("kwargs,launches", [
     (dict(lengths=(), num_chunks=0), 0),
+    (dict(lengths=(0, 0), k=0, o=0, lse=0), 0),
+    (dict(), 4),
+    (dict(lengths=(64, 0, 5)), 4),
+    (dict(num_splits=2, ws=FAKE, ws_bytes=1 << 30), 5),  # the second chunk's merge
 ])
-def test_refused_before_anything_is_enqueued(mocap_lib, kwargs, expect):
-    assert _call(mocap_lib.load_library(), **kwargs) == expect
+def test_accepted(host_lib, kwargs, launches):
+    before = host_lib.record_launches()
+    assert _call(host_lib, **kwargs) == 0
+    assert host_lib.record_launches() - before == launches
 
 
 @pytest.mark.gpu
@@ -77,6 +113,16 @@ def test_inputs_the_loop_refuses_stay_refused(gpu):
         r.run(q, k.view(128, 1, 128), v.view(128, 1, 128), 0.1)  # other heads
     with pytest.raises(ValueError):
         r.run(q, k, v.cpu(), 0.1)
+    before = r.store.k_pool.view(torch.int16).clone(), r.store.v_pool.view(torch.int16).clone()
     with pytest.raises(binding.MocapError) as e:
         r.run(q, k, v, 0.0)
     assert e.value.status == INVALID
+    r.num_splits = 3  # a plan that needs more than the workspace
+    with pytest.raises(binding.MocapError) as e:
+        r.run(q, k, v, 0.1)
+    assert e.value.status == WORKSPACE
+    for lengths in ([90, -10, 48], [-5, 5], [64, 64, 1]):
+        with pytest.raises(ValueError):
+            binding.mocap_chunk_prefill(r.store, r.table, lengths, q, k, v, 0.1, r.o, r._lse_flat, r.workspace)
+    assert torch.equal(r.store.k_pool.view(torch.int16), before[0])
+    assert torch.equal(r.store.v_pool.view(torch.int16), before[1])
