@@ -144,7 +144,7 @@ int workgroups_of_rows(int64_t rows, int pairing) {
                                     : (groups + 1) / 2);
 }
 
-// Estimates of `limit` or more may be returned early, from the mean load alone.
+// Infinity if the mean load alone reaches `limit`.
 double estimate_launch_us(const LaunchShape& x, int n_ranges, bool own_range, int pairing, double limit) {
   const int group = x.h_q / x.h_kv;
   const int64_t rows = (int64_t)x.chunk_len * group;
@@ -193,7 +193,7 @@ double estimate_launch_us(const LaunchShape& x, int n_ranges, bool own_range, in
   double sum = 0.0;
   for (double c : cost) sum += c;
   const double mean = sum * x.h_kv / (xcd_slots * kXcds);
-  if (fixed + mean >= limit) return fixed + mean;
+  if (fixed + mean >= limit) return INFINITY;
   double makespan = 0.0;
   int64_t next = 0;
   const int64_t size = (int64_t)cost.size();
@@ -241,10 +241,11 @@ int pairing_mode() {
 // throughout, workgroups of different lengths evened out when there are many
 // per compute unit; single: both units on one row group's tiles, half of each
 // tile's keys, which pays where even then compute units stay free).
-double best_pairing_us(const LaunchShape& x, int n_ranges, bool own_range, double limit, int* pairing_out) {
+double best_pairing_us(const LaunchShape& x, int n_ranges, bool own_range, int* pairing_out) {
   const int mode = pairing_mode();
   int best = mode >= 0 ? mode : kMirrored;
-  double best_us = estimate_launch_us(x, n_ranges, own_range, best, limit);
+  // In full, also where it is too long: the others are measured by it.
+  double best_us = estimate_launch_us(x, n_ranges, own_range, best, INFINITY);
   if (mode < 0) {
     // Another placement only when the model expects it to win clearly.  With
     // up to two row groups the two ways to pair them are the same, with one
@@ -256,7 +257,7 @@ double best_pairing_us(const LaunchShape& x, int n_ranges, bool own_range, doubl
       if (pairing == kSingle && (x.row_groups <= 1 || wgs > kSingleRounds * x.slots)) continue;
       if (pairing == kShort && wgs > kShortRounds * x.slots) continue;
       const double bar = best_us * (pairing == kShort ? 0.95 : 0.98);
-      const double us = estimate_launch_us(x, n_ranges, own_range, pairing, std::min(limit, bar));
+      const double us = estimate_launch_us(x, n_ranges, own_range, pairing, bar);
       if (us < bar) {
         best_us = us;
         best = pairing;
@@ -314,10 +315,10 @@ int choose_ranges(const LaunchShape& x, int base_wgs, int64_t prefix_tiles, int 
   }
   int best = 1;
   // A split must pay for itself clearly.
-  double best_us = 0.98 * best_pairing_us(x, 1, false, INFINITY, nullptr);
+  double best_us = 0.98 * best_pairing_us(x, 1, false, nullptr);
   auto consider = [&](int64_t n) {
     if (workspace_for((int)n, x.chunk_len, x.h_q, x.head_dim) > ws_cap) return;
-    const double us = best_pairing_us(x, (int)n, false, best_us, nullptr);
+    const double us = best_pairing_us(x, (int)n, false, nullptr);
     if (us < best_us) {
       best_us = us;
       best = (int)n;
@@ -434,7 +435,7 @@ int choose_pairing(const Plan& plan, int64_t prefix_len, int32_t chunk_len, int3
   }
   int pairing = kMirrored;
   best_pairing_us(LaunchShape{prefix_len, chunk_len, h_q, h_kv, head_dim, plan.row_groups, std::max(cus, 1)},
-                  plan.n_ranges, plan.own_range, INFINITY, &pairing);
+                  plan.n_ranges, plan.own_range, &pairing);
   std::lock_guard<std::mutex> lock(g_plan_mutex);
   g_pair_keys[g_pair_next] = key;
   g_pair_values[g_pair_next] = pairing;

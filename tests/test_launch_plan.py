@@ -1,0 +1,139 @@
+"""The automatic choice of KV ranges and placement against the whole model
+written out: every candidate estimated in full, workgroup by workgroup."""
+import ctypes
+import heapq
+import math
+import random
+
+import pytest
+
+from paper_2606_22968_amd import binding
+
+FAKE = 0x10000  # aligned, never dereferenced
+CUS, XCDS = 256, 8
+MIRRORED, ADJACENT, SINGLE, SHORT = range(4)
+HEADS = [(32, 8, 128), (64, 8, 128), (8, 8, 64), (8, 2, 128), (16, 2, 64), (12, 4, 128), (32, 1, 128), (64, 1, 64),
+         (6, 3, 128), (5, 5, 128)]
+
+
+def library_choice(lib, prefix, length, h_q, h_kv, d, splits=0):
+    """(placement, ranges) of the launch that the library makes."""
+    store = binding.mocap_kv_store(FAKE, FAKE, 1 << 22, 64, h_kv, d)
+    ranges, size = ctypes.c_int32(), ctypes.c_size_t()
+    assert lib.mocap_chunk_attn_workspace_size(prefix, length, h_q, h_kv, d, splits, ctypes.byref(ranges),
+                                               ctypes.byref(size)) == 0
+    assert lib.mocap_chunk_attn(ctypes.byref(store), FAKE, 1 << 22, FAKE, prefix, length, h_q, h_kv, d, 0.1, FAKE,
+                                FAKE, FAKE, size.value, splits, None) == 0
+    out = (ctypes.c_int * 3)()
+    lib.record_last(out)
+    assert out[1] == ranges.value
+    return out[0], out[1]
+
+
+def workgroups(rows, placement):
+    groups = -(-rows // 128)
+    return -(-rows // 32) if placement == SHORT else groups if placement == SINGLE else -(-groups // 2)
+
+
+def estimate(prefix, length, h_q, h_kv, d, n, own, placement):
+    """Modelled time of one launch in us."""
+    group = h_q // h_kv
+    rows = length * group
+    unit = 32 if placement == SHORT else 128
+    groups, pairs = -(-rows // unit), workgroups(rows, placement)
+    tile_us, group_us, step_us = (1.25, 5.0, 1.5) if d == 128 else (0.8, 3.5, 0.8)
+    all_tiles = -(-(prefix + length) // 64)
+    parts, span = (n - 1, -(-prefix // 64)) if own else (n, all_tiles)
+    ends = [-(-(prefix + min(length, -(-(g + 1) * unit // group))) // 64) for g in range(groups)]
+    cost = []
+    for r in range(n):
+        t0, t1 = (span * r // parts, span * (r + 1) // parts) if r < parts else (prefix // 64, all_tiles)
+        for q in range(pairs):
+            top = groups - 1 - (2 * q if placement == ADJACENT else q)
+            other = -1 if placement >= SINGLE else top - 1 if placement == ADJACENT else q if q < top else -1
+            a = max(0, min(t1, ends[top]) - t0)
+            b = max(0, min(t1, ends[other]) - t0) if other >= 0 else 0
+            if placement == SHORT:
+                cost.append(-(-2 * a // 8) * step_us + 2.0)
+            else:
+                cost.append((min(a, b) + abs(a - b) * 0.65) * tile_us + group_us)
+    makespan, first, total = 0.0, 0, len(cost) * h_kv
+    done = set()
+    for x in range(XCDS):
+        count = total // XCDS + (x < total % XCDS)
+        if (first % len(cost), count) not in done:
+            done.add((first % len(cost), count))
+            busy = [0.0] * (CUS // XCDS)
+            for i in range(first, first + count):
+                t = busy[0] + cost[i % len(cost)]
+                heapq.heapreplace(busy, t)
+                makespan = max(makespan, t)
+        first += count
+    us = 6.0
+    if n > 1:
+        us += 2.0 * n * length * h_q * (d + 1) * 4.0 / 5e6 + 6.0
+    stream = 4.0 * (prefix + length) * h_kv * d / (4.2e6 if placement == SHORT else 4.7e6)
+    return us + math.hypot(makespan, 0.6 * stream)
+
+
+def best_placement(prefix, length, h_q, h_kv, d, n, own):
+    rows = length * (h_q // h_kv)
+    groups = -(-rows // 128)
+    best, best_us = MIRRORED, estimate(prefix, length, h_q, h_kv, d, n, own, MIRRORED)
+    for placement in (ADJACENT, SINGLE, SHORT):
+        wgs = workgroups(rows, placement) * h_kv * n
+        if (placement == ADJACENT and groups <= 2) or (placement == SINGLE and (groups <= 1 or wgs > 2 * CUS)) or \
+                (placement == SHORT and wgs > 4 * CUS):
+            continue
+        us = estimate(prefix, length, h_q, h_kv, d, n, own, placement)
+        if us < best_us * (0.95 if placement == SHORT else 0.98):
+            best, best_us = placement, us
+    return best, best_us
+
+
+def model_choices(prefix, length, h_q, h_kv, d):
+    """The (placement, ranges) pairs that are best (more than one only in a tie)."""
+    rows = length * (h_q // h_kv)
+    all_tiles = -(-(prefix + length) // 64)
+    base = h_kv * -(-(-(-rows // 128)) // 2)
+    max_n = min(all_tiles // 4, max(min(8, 4096 // base), 2048 // base))
+    counts = set(range(2, min(16, max_n) + 1))
+    for k in range(1, 2048 // CUS + 1):
+        for placement in (MIRRORED, SINGLE, SHORT):
+            n = k * CUS // (workgroups(rows, placement) * h_kv)
+            if 16 < n <= max_n:
+                counts.add(n)
+    unsplit = best_placement(prefix, length, h_q, h_kv, d, 1, False)
+    plans = {n: best_placement(prefix, length, h_q, h_kv, d, n, False) for n in counts}
+    low = min((us for _, us in plans.values()), default=math.inf)
+    bar = 0.98 * unsplit[1]
+    eps = 1e-9 * bar
+    out = [(p, n) for n, (p, us) in plans.items() if us <= low + eps and us < bar + eps]
+    return out + [(unsplit[0], 1)] if low >= bar - eps else out
+
+
+def shapes(count, seed, longest=2048):
+    rng = random.Random(seed)
+
+    def log(lo, hi):
+        return round(math.exp(rng.uniform(math.log(lo), math.log(hi))))
+    return [(log(1, 300000), log(1, longest), *rng.choice(HEADS)) for _ in range(count)]
+
+
+@pytest.mark.parametrize("shape", [
+    (12755, 8, 32, 8, 128), (13496, 6837, 32, 8, 128),           # another placement wins where mirrored cannot
+    (9001, 7, 32, 8, 128), (23040, 10, 16, 2, 64), (30720, 137, 32, 8, 128), (126976, 4096, 32, 8, 128),
+    (64, 1, 8, 8, 64), (63, 64, 32, 8, 128), (300000, 1, 32, 1, 128), (1048276, 300, 32, 8, 128),
+] + shapes(50, 5))
+def test_automatic_plan_is_the_models_best(host_lib, shape):
+    got, want = library_choice(host_lib, *shape), model_choices(*shape)
+    print(shape, got, want)
+    assert got in want
+
+
+@pytest.mark.parametrize("splits", [1, 2, 5, 64, 700])
+@pytest.mark.parametrize("shape", shapes(12, 6, 300) + [(100000, 1, 32, 8, 128), (130, 9, 8, 8, 64)])
+def test_placement_of_requested_ranges(host_lib, shape, splits):
+    placement, n = library_choice(host_lib, *shape, splits=splits)
+    assert n == min(splits, -(-shape[0] // 64) + 1)
+    assert placement == best_placement(*shape, n, n > 1)[0]
