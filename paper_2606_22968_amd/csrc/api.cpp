@@ -7,11 +7,11 @@
 
 #include <algorithm>
 #include <atomic>
+#include <bitset>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
-#include <functional>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -73,6 +73,7 @@ struct Plan {
   int64_t units;     // size of the chunk (bounded by make_plan)
   int64_t prefix_tiles;
   int n_ranges;
+  int pairing;       // -1: not chosen with the ranges
   bool own_range;    // the chunk's own keys are a range of their own (requested splits)
   size_t ws_bytes;
   // Prefix tiles [remote_begin, remote_end) come from a second store.
@@ -144,85 +145,279 @@ int workgroups_of_rows(int64_t rows, int pairing) {
                                     : (groups + 1) / 2);
 }
 
-// Infinity if the mean load alone reaches `limit`.
-double estimate_launch_us(const LaunchShape& x, int n_ranges, bool own_range, int pairing, double limit) {
-  const int group = x.h_q / x.h_kv;
-  const int64_t rows = (int64_t)x.chunk_len * group;
-  const int unit_rows = pairing == kShort ? kAttnWaveRows : kUnitRows;
-  const int row_groups = (int)((rows + unit_rows - 1) / unit_rows);
-  const int pairs = workgroups_of_rows(rows, pairing);
-  const double group_us = x.head_dim == 128 ? kGroupUs128 : kGroupUs64;
-  const double step_us = x.head_dim == 128 ? kStepUs128 : kStepUs64;
-  const double tile_us = x.head_dim == 128 ? kTileUs128 : kTileUs64;
-  const int64_t prefix_tiles = (x.prefix_len + kTileKeys - 1) / kTileKeys;
-  const int64_t all_tiles = (x.prefix_len + x.chunk_len + kTileKeys - 1) / kTileKeys;
-  const int parts = own_range ? n_ranges - 1 : n_ranges;
-  const int64_t span = own_range ? prefix_tiles : all_tiles;
-  // Tiles the unit of row group rg visits among tiles [t0, t1).
-  auto unit_tiles = [&](int rg, int64_t t0, int64_t t1) -> int64_t {
-    if (rg < 0) return 0;
-    const int64_t tokens = std::min<int64_t>(x.chunk_len, ((int64_t)(rg + 1) * unit_rows + group - 1) / group);
-    const int64_t end = (x.prefix_len + tokens + kTileKeys - 1) / kTileKeys;
-    return std::max<int64_t>(0, std::min(t1, end) - t0);
+// The model above.  A caller whose prefix moves plans on every call, so this
+// has to stay short of the launch it plans.  Almost all workgroups of a launch
+// cost the same: costs are made as they are handed out, the compute units'
+// finishing times stay in a sorted ring (a new one goes in near its end), and
+// bounds made without any of that leave few candidates to walk through.
+// Planning a new shape, up to 512 tokens behind up to 10^6 keys: 12 us on
+// average, 63 at the 99th percentile; with an array of all costs and a heap for
+// every candidate 72 and 450.
+class LaunchModel {
+ public:
+  LaunchModel(const LaunchShape& x, bool own_range)
+      : x_(x), group_(x.h_q / x.h_kv), rows_((int64_t)x.chunk_len * group_), own_(own_range),
+        all_tiles_((x.prefix_len + x.chunk_len + kTileKeys - 1) / kTileKeys),
+        span_(own_range ? (x.prefix_len + kTileKeys - 1) / kTileKeys : all_tiles_),
+        xcd_slots_(std::min(std::max(1, x.slots / kXcds), kRing)),
+        tile_us_(x.head_dim == 128 ? kTileUs128 : kTileUs64), group_us_(x.head_dim == 128 ? kGroupUs128 : kGroupUs64),
+        step_us_(x.head_dim == 128 ? kStepUs128 : kStepUs64) {
+    for (int pairing : {kMirrored, kAdjacent, kSingle, kShort}) lay_out(pairing);
+  }
+
+  // The best placement of row groups in workgroups (mirrored: q with R-1-q,
+  // every workgroup about equally long, the units sharing the tiles only the
+  // longer one sees; adjacent: 2q with 2q+1, both units on their own rows nearly
+  // throughout, workgroups of different lengths evened out when there are many
+  // per compute unit; single: both units on one row group's tiles, half of each
+  // tile's keys, which pays where even then compute units stay free; short: the
+  // other kernel).  In this order, another one only when the model expects it to
+  // win clearly over the best so far.  Returns its time, or infinity if no
+  // placement stays under `limit`; with us_out null the time is not made.
+  int best(int n_ranges, double limit, int forced, double* us_out) const {
+    if (forced >= 0) {
+      if (us_out) *us_out = bound(forced, n_ranges) < limit ? estimate(forced, n_ranges, limit) : INFINITY;
+      return forced;
+    }
+    // With up to two row groups the two ways to pair them are the same, with
+    // one so is single.
+    const int64_t groups = layout_[kMirrored].units;
+    const bool open[4] = {true, groups > 2,
+                          groups > 1 && layout_[kSingle].wgs * x_.h_kv * n_ranges <= kSingleRounds * x_.slots,
+                          layout_[kShort].wgs * x_.h_kv * n_ranges <= kShortRounds * x_.slots};
+    constexpr double bar[4] = {1.0, 0.98, 0.98, 0.95};
+    double lo[4], hi[4];  // the time lies between
+    double least = INFINITY;
+    for (int p = kMirrored; p <= kShort; ++p) {
+      lo[p] = hi[p] = INFINITY;
+      if (!open[p]) continue;
+      lo[p] = bound(p, n_ranges);
+      if (limit < INFINITY) {
+        const double us = lo[p] < limit ? estimate(p, n_ranges, limit) : INFINITY;
+        lo[p] = us < INFINITY ? us : std::max(lo[p], limit);
+        hi[p] = us;
+      } else {
+        hi[p] = upper_bound(p, n_ranges);
+      }
+      least = std::min(least, lo[p]);
+    }
+    if (least >= limit) {
+      if (us_out) *us_out = INFINITY;
+      return kMirrored;
+    }
+    auto settle = [&](int p) { lo[p] = hi[p] = estimate(p, n_ranges, INFINITY); };
+    // The last one that wins over every one before it; then one by one.
+    int best = kMirrored;
+    double before = lo[kMirrored];
+    for (int p = kAdjacent; p <= kShort; ++p) {
+      if (open[p] && hi[p] < bar[p] * before) best = p;
+      before = std::min(before, lo[p]);
+    }
+    for (int p = best + 1; p <= kShort; ++p) {
+      if (!open[p]) continue;
+      while (hi[p] >= bar[p] * lo[best] && lo[p] < bar[p] * hi[best] && (lo[best] < hi[best] || lo[p] < hi[p]))
+        settle(lo[best] < hi[best] ? best : p);
+      if (hi[p] < bar[p] * lo[best]) best = p;
+    }
+    if (us_out) {
+      if (lo[best] < hi[best]) settle(best);
+      *us_out = hi[best];
+    }
+    return best;
+  }
+
+  // A lower bound of the time of any placement.
+  double least(int n_ranges) const {
+    double us = INFINITY;
+    for (int p : {kMirrored, kAdjacent, kSingle, kShort}) us = std::min(us, bound(p, n_ranges));
+    return us;
+  }
+
+ private:
+  static constexpr int kRing = 256;  // compute units of an XCD, at most
+
+  struct Layout {
+    int64_t units;  // row groups, or 32-row slots (short)
+    int64_t wgs;    // workgroups of one KV head and range
+    bool lone;      // the last of them has one row group where the others have two
+    double work;    // tiles of one KV head's workgroups over the whole span, in units of kTileUs
   };
-  std::vector<double> cost;  // of one KV head, in logical order
-  cost.reserve((size_t)pairs * n_ranges);
-  for (int r = 0; r < n_ranges; ++r) {
-    const int64_t t0 = r < parts ? span * r / parts : x.prefix_len / kTileKeys;
-    const int64_t t1 = r < parts ? span * (r + 1) / parts : all_tiles;
-    for (int q = 0; q < pairs; ++q) {
-      // Pair q: row groups q and R-1-q, R-2-2q and R-1-2q, or R-1-q alone.
-      const int top = pairing == kAdjacent ? row_groups - 1 - 2 * q : row_groups - 1 - q;
-      const int other = pairing >= kSingle ? -1 : pairing == kAdjacent ? top - 1 : q < top ? q : -1;
-      const int64_t a = unit_tiles(top, t0, t1), b = unit_tiles(other, t0, t1);
-      if (pairing == kShort) {
-        cost.push_back((double)((2 * a + kAttnWaves - 1) / kAttnWaves) * step_us + kShortGroupUs);
-      } else {
-        cost.push_back(((double)std::min(a, b) + (double)(std::max(a, b) - std::min(a, b)) * kLoneTile) * tile_us +
-                       group_us);
-      }
+
+  // The end of the tiles that row group (or slot) u sees.
+  int64_t unit_end(int64_t u, int unit_rows) const {
+    const int64_t tokens = std::min<int64_t>(x_.chunk_len, ((u + 1) * unit_rows + group_ - 1) / group_);
+    return (x_.prefix_len + tokens + kTileKeys - 1) / kTileKeys;
+  }
+  static int unit_rows(int pairing) { return pairing == kShort ? kAttnWaveRows : kUnitRows; }
+
+  // The row groups of workgroup q (the lower one -1: none): q and R-1-q, R-2-2q
+  // and R-1-2q, or R-1-q alone.
+  void groups_of(int pairing, int64_t q, int64_t* top, int64_t* other) const {
+    const int64_t last = layout_[pairing].units - 1;
+    *top = pairing == kAdjacent ? last - 2 * q : last - q;
+    *other = pairing >= kSingle ? -1 : pairing == kAdjacent ? *top - 1 : q < *top ? q : -1;
+  }
+
+  // Cost of a workgroup whose row groups see a and b of a range's tiles (b = 0: alone).
+  double cost_of(int pairing, int64_t a, int64_t b) const {
+    if (pairing == kShort) return (double)((2 * a + kAttnWaves - 1) / kAttnWaves) * step_us_ + kShortGroupUs;
+    return ((double)b + (double)(a - b) * kLoneTile) * tile_us_ + group_us_;
+  }
+
+  void lay_out(int pairing) {
+    Layout& l = layout_[pairing];
+    l.units = (rows_ + unit_rows(pairing) - 1) / unit_rows(pairing);
+    l.wgs = workgroups_of_rows(rows_, pairing);
+    l.lone = pairing < kSingle && l.units % 2 != 0;
+    // Sum over the span: its ranges cover each row group's tiles once (the tile
+    // of the prefix's end twice if the chunk's keys are a range of their own).
+    const int64_t twice = own_ ? span_ - x_.prefix_len / kTileKeys : 0;
+    l.work = 0.0;
+    for (int64_t q = 0; q < l.wgs; ++q) {
+      int64_t top, other;
+      groups_of(pairing, q, &top, &other);
+      const double a = (double)(unit_end(top, unit_rows(pairing)) + twice);
+      const double b = other >= 0 ? (double)(unit_end(other, unit_rows(pairing)) + twice) : 0.0;
+      l.work += pairing == kShort ? a : b + (a - b) * kLoneTile;
     }
   }
-  double fixed = kLaunchUs;
-  if (n_ranges > 1) {
-    const double partial = (double)n_ranges * x.chunk_len * x.h_q * (x.head_dim + 1) * 4.0;
-    fixed += 2.0 * partial / kMergeBytesPerUs + kLaunchUs;
+
+  double stream_us(int pairing) const {
+    return kStreamWeight * (4.0 * (x_.prefix_len + x_.chunk_len) * x_.h_kv * x_.head_dim /
+                            (pairing == kShort ? kShortBytesPerUs : kTileBytesPerUs));
   }
-  const int64_t total_wgs = (int64_t)cost.size() * x.h_kv;
-  const int xcd_slots = std::max(1, x.slots / kXcds);
-  double sum = 0.0;
-  for (double c : cost) sum += c;
-  const double mean = sum * x.h_kv / (xcd_slots * kXcds);
-  if (fixed + mean >= limit) return INFINITY;
-  double makespan = 0.0;
-  int64_t next = 0;
-  const int64_t size = (int64_t)cost.size();
-  std::pair<int64_t, int64_t> seen[kXcds];  // (first workgroup of its KV head, count) of the XCDs so far
-  std::vector<double> busy_until;
-  for (int xcd = 0; xcd < kXcds; ++xcd) {
-    const int64_t begin = next, count = total_wgs / kXcds + (xcd < total_wgs % kXcds ? 1 : 0);
-    next += count;
-    seen[xcd] = {begin % size, count};
-    if (std::find(seen, seen + xcd, seen[xcd]) != seen + xcd) continue;  // runs the same workgroups
-    busy_until.clear();
-    for (int64_t i = begin; i < next; ++i) {
-      double t = cost[(size_t)(i % size)];
-      if ((int)busy_until.size() == xcd_slots) {
-        if (i - begin == xcd_slots) std::make_heap(busy_until.begin(), busy_until.end(), std::greater<double>());
-        std::pop_heap(busy_until.begin(), busy_until.end(), std::greater<double>());
-        t += busy_until.back();
-        busy_until.back() = t;
-        std::push_heap(busy_until.begin(), busy_until.end(), std::greater<double>());
-      } else {
-        busy_until.push_back(t);
-      }
-      makespan = std::max(makespan, t);
+  double fixed_us(int n_ranges) const {
+    if (n_ranges <= 1) return kLaunchUs;
+    const double partial = (double)n_ranges * x_.chunk_len * x_.h_q * (x_.head_dim + 1) * 4.0;
+    return kLaunchUs + 2.0 * partial / kMergeBytesPerUs + kLaunchUs;
+  }
+  static double total_us(double fixed, double makespan, double stream) {
+    return fixed + std::sqrt(makespan * makespan + stream * stream);
+  }
+
+  // At least the mean load of a compute unit; and the ranges that every row
+  // sees in full cost the same up to one tile, so some compute unit gets a
+  // whole number of those.
+  double bound(int pairing, int n_ranges) const {
+    const Layout& l = layout_[pairing];
+    const double per_tile = pairing == kShort ? 2.0 / kAttnWaves * step_us_ : tile_us_;
+    const double per_wg = pairing == kShort ? kShortGroupUs : group_us_;
+    double load = (l.work * per_tile + (double)(l.wgs * n_ranges) * per_wg) * x_.h_kv / (xcd_slots_ * kXcds);
+    const int64_t parts = own_ ? n_ranges - 1 : n_ranges;
+    if (parts > 0 && l.wgs > 0) {
+      const int64_t seen = x_.prefix_len / kTileKeys + 1;  // tiles that every row sees
+      const int64_t inner = own_ ? parts : std::min<int64_t>(parts, ((seen + 1) * parts - 1) / span_);
+      // Those with a pair of row groups, and all of them at the cost of the lone one.
+      const int64_t tiles = span_ / parts;
+      auto least_of = [&](int64_t wgs, bool pair) {
+        const int64_t jobs = inner * wgs * x_.h_kv;
+        const int64_t rounds = ((jobs + kXcds - 1) / kXcds + xcd_slots_ - 1) / xcd_slots_;
+        const int64_t t = tiles + (rounds == 1 && span_ % parts > parts - inner ? 1 : 0);
+        load = std::max(load, (double)rounds * cost_of(pairing, t, pair ? t : 0));
+      };
+      if (pairing < kSingle && l.wgs > (l.lone ? 1 : 0)) least_of(l.wgs - (l.lone ? 1 : 0), true);
+      if (pairing >= kSingle || l.lone) least_of(l.wgs, false);
     }
+    // Rounding of the sums aside.
+    return total_us(fixed_us(n_ranges), load, stream_us(pairing)) * (1.0 - 1e-9);
   }
-  const double kv_us = 4.0 * (x.prefix_len + x.chunk_len) * x.h_kv * x.head_dim /
-                       (pairing == kShort ? kShortBytesPerUs : kTileBytesPerUs);
-  return fixed + std::hypot(makespan, kStreamWeight * kv_us);
-}
+
+  // At most: the longest workgroup behind the mean of as many of them.
+  double upper_bound(int pairing, int n_ranges) const {
+    const Layout& l = layout_[pairing];
+    const int64_t parts = own_ ? n_ranges - 1 : n_ranges;
+    int64_t tiles = parts > 0 ? (span_ + parts - 1) / parts : 0;
+    if (own_) tiles = std::max(tiles, all_tiles_ - x_.prefix_len / kTileKeys);
+    const double longest = cost_of(pairing, tiles, pairing < kSingle && l.units > 1 ? tiles : 0);
+    const int64_t jobs = (l.wgs * n_ranges * x_.h_kv + kXcds - 1) / kXcds;
+    const double rounds = jobs <= xcd_slots_ ? 1.0 : (double)jobs / xcd_slots_ + 1.0;
+    return total_us(fixed_us(n_ranges), rounds * longest, stream_us(pairing)) * (1.0 + 1e-9);
+  }
+
+  // Infinity if it is certain to reach `limit`.
+  double estimate(int pairing, int n_ranges, double limit) const {
+    const double fixed = fixed_us(n_ranges), stream = stream_us(pairing);
+    double longest = INFINITY;  // makespan
+    if (limit < INFINITY) {
+      const double rest = limit - fixed;
+      if (rest <= stream) return INFINITY;
+      longest = std::sqrt(rest * rest - stream * stream) * (1.0 + 1e-9);
+    }
+    const double makespan = simulate(pairing, n_ranges, longest);
+    return makespan < INFINITY ? total_us(fixed, makespan, stream) : INFINITY;
+  }
+
+  // The workgroups in the order in which the hardware hands them out; infinity
+  // if one ends after `longest`.
+  double simulate(int pairing, int n_ranges, double longest) const {
+    const Layout& l = layout_[pairing];
+    const int64_t size = l.wgs * n_ranges;  // workgroups of one KV head
+    const int64_t total = size * x_.h_kv;
+    const int64_t parts = own_ ? n_ranges - 1 : n_ranges;
+    const int64_t seen = x_.prefix_len / kTileKeys + 1;
+    const int rows = unit_rows(pairing);
+    std::pair<int64_t, int64_t> done[kXcds];  // (first workgroup of its KV head, count) of the XCDs so far
+    double makespan = 0.0;
+    double ring[kRing];
+    int64_t next = 0;
+    for (int xcd = 0; xcd < kXcds; ++xcd) {
+      const int64_t count = total / kXcds + (xcd < total % kXcds ? 1 : 0);
+      done[xcd] = {next % size, count};
+      next += count;
+      if (std::find(done, done + xcd, done[xcd]) != done + xcd) continue;  // runs the same workgroups
+      int head = 0, busy = 0;  // ring[head ..] holds `busy` times in ascending order
+      auto hand_out = [&](double t) {
+        if (busy == xcd_slots_) {
+          t += ring[head];
+          head = (head + 1) & (kRing - 1);
+        } else {
+          ++busy;
+        }
+        int at = (head + busy - 1) & (kRing - 1);
+        for (int i = busy - 1; i > 0; --i) {
+          const int before = (at + kRing - 1) & (kRing - 1);
+          if (ring[before] <= t) break;
+          ring[at] = ring[before];
+          at = before;
+        }
+        ring[at] = t;
+      };
+      int64_t r = done[xcd].first / l.wgs, q = done[xcd].first % l.wgs;
+      for (int64_t left = count; left > 0;) {
+        const int64_t t0 = r < parts ? span_ * r / parts : x_.prefix_len / kTileKeys;
+        const int64_t t1 = r < parts ? span_ * (r + 1) / parts : all_tiles_;
+        const int64_t stop = q + std::min(l.wgs - q, left);
+        left -= stop - q;
+        const bool inner = t1 <= seen;
+        const double full = cost_of(pairing, t1 - t0, pairing < kSingle ? t1 - t0 : 0);
+        for (; q < stop; ++q) {
+          if (inner && !(l.lone && q == l.wgs - 1)) {
+            hand_out(full);
+            continue;
+          }
+          int64_t top, other;
+          groups_of(pairing, q, &top, &other);
+          const int64_t a = std::max<int64_t>(0, std::min(t1, unit_end(top, rows)) - t0);
+          const int64_t b = other >= 0 ? std::max<int64_t>(0, std::min(t1, unit_end(other, rows)) - t0) : 0;
+          hand_out(cost_of(pairing, a, b));
+        }
+        if (busy > 0 && ring[(head + busy - 1) & (kRing - 1)] > longest) return INFINITY;
+        q = 0;
+        r = r + 1 == n_ranges ? 0 : r + 1;
+      }
+      if (busy > 0) makespan = std::max(makespan, ring[(head + busy - 1) & (kRing - 1)]);
+    }
+    return makespan;
+  }
+
+  const LaunchShape& x_;
+  const int64_t group_, rows_;
+  const bool own_;
+  const int64_t all_tiles_, span_;
+  const int xcd_slots_;
+  const double tile_us_, group_us_, step_us_;
+  Layout layout_[4];
+};
 
 // MOCAP_PAIRING=mirrored, =adjacent, =single or =short in the environment forces a
 // pairing (for tests); -1 = choose.
@@ -233,39 +428,6 @@ int pairing_mode() {
   if (force && std::strcmp(force, "single") == 0) return kSingle;
   if (force && std::strcmp(force, "short") == 0) return kShort;
   return -1;
-}
-
-// The best placement of row groups in workgroups (mirrored: q with R-1-q,
-// every workgroup about equally long, the units sharing the tiles only the
-// longer one sees; adjacent: 2q with 2q+1, both units on their own rows nearly
-// throughout, workgroups of different lengths evened out when there are many
-// per compute unit; single: both units on one row group's tiles, half of each
-// tile's keys, which pays where even then compute units stay free).
-double best_pairing_us(const LaunchShape& x, int n_ranges, bool own_range, int* pairing_out) {
-  const int mode = pairing_mode();
-  int best = mode >= 0 ? mode : kMirrored;
-  // In full, also where it is too long: the others are measured by it.
-  double best_us = estimate_launch_us(x, n_ranges, own_range, best, INFINITY);
-  if (mode < 0) {
-    // Another placement only when the model expects it to win clearly.  With
-    // up to two row groups the two ways to pair them are the same, with one
-    // so is single.
-    const int64_t rows = (int64_t)x.chunk_len * (x.h_q / x.h_kv);
-    for (int pairing : {kAdjacent, kSingle, kShort}) {
-      const int64_t wgs = (int64_t)workgroups_of_rows(rows, pairing) * x.h_kv * n_ranges;
-      if (pairing == kAdjacent && x.row_groups <= 2) continue;
-      if (pairing == kSingle && (x.row_groups <= 1 || wgs > kSingleRounds * x.slots)) continue;
-      if (pairing == kShort && wgs > kShortRounds * x.slots) continue;
-      const double bar = best_us * (pairing == kShort ? 0.95 : 0.98);
-      const double us = estimate_launch_us(x, n_ranges, own_range, pairing, bar);
-      if (us < bar) {
-        best_us = us;
-        best = pairing;
-      }
-    }
-  }
-  if (pairing_out) *pairing_out = best;
-  return best_us;
 }
 
 struct PlanKey {
@@ -285,7 +447,7 @@ struct PlanKey {
 std::mutex g_plan_mutex;
 constexpr int kPlanCache = 64;
 PlanKey g_plan_keys[kPlanCache];
-int g_plan_values[kPlanCache];
+std::pair<int, int> g_plan_values[kPlanCache];  // ranges, pairing
 int g_plan_count = 0, g_plan_next = 0;
 
 // Most workgroups of a split launch (of few ranges, which even out the long
@@ -300,7 +462,9 @@ constexpr int64_t kMinRangeTiles = 4;
 // plan with the smallest modelled launch time among no split and even cuts of
 // all keys whose workspace fits in ws_cap bytes: any count up to 16, and above
 // that the counts that fill the compute units a whole number of times.
-int choose_ranges(const LaunchShape& x, int base_wgs, int64_t prefix_tiles, int requested, size_t ws_cap) {
+int choose_ranges(const LaunchShape& x, int base_wgs, int64_t prefix_tiles, int requested, size_t ws_cap,
+                  int* pairing_out) {
+  *pairing_out = -1;
   if (prefix_tiles <= 0) return 1;
   if (requested >= 1) {
     if (requested == 1) return 1;
@@ -311,34 +475,59 @@ int choose_ranges(const LaunchShape& x, int base_wgs, int64_t prefix_tiles, int 
   {
     std::lock_guard<std::mutex> lock(g_plan_mutex);
     for (int i = 0; i < g_plan_count; ++i)
-      if (g_plan_keys[i] == key) return g_plan_values[i];
+      if (g_plan_keys[i] == key) {
+        *pairing_out = g_plan_values[i].second;
+        return g_plan_values[i].first;
+      }
   }
+  const LaunchModel model(x, false);
+  const int mode = pairing_mode();
   int best = 1;
-  // A split must pay for itself clearly.
-  double best_us = 0.98 * best_pairing_us(x, 1, false, nullptr);
+  double best_us;
+  int pairing = model.best(1, INFINITY, mode, &best_us);
+  best_us *= 0.98;  // a split must pay for itself clearly
+  std::bitset<kSplitWgsMany + 1> tried;  // counts above 8 are at most kSplitWgsMany
   auto consider = [&](int64_t n) {
-    if (workspace_for((int)n, x.chunk_len, x.h_q, x.head_dim) > ws_cap) return;
-    const double us = best_pairing_us(x, (int)n, false, nullptr);
-    if (us < best_us) {
+    if (tried[(size_t)n] || workspace_for((int)n, x.chunk_len, x.h_q, x.head_dim) > ws_cap) return;
+    tried[(size_t)n] = true;
+    double us;
+    const int with = model.best((int)n, best_us, mode, &us);
+    if (us < best_us || (us == best_us && best > 1 && n < best)) {
       best_us = us;
       best = (int)n;
+      pairing = with;
     }
   };
   const int64_t all_tiles = (x.prefix_len + x.chunk_len + kTileKeys - 1) / kTileKeys;
   const int64_t max_n = std::min(all_tiles / kMinRangeTiles,
                                  std::max(std::min(kFewRanges, kSplitWgsFew / base_wgs), kSplitWgsMany / base_wgs));
-  for (int64_t n = 2; n <= std::min<int64_t>(16, max_n); ++n) consider(n);
-  for (int64_t k = 1; k * x.slots <= kSplitWgsMany; ++k) {
-    for (const int pairing : {kMirrored, kSingle, kShort}) {
-      const int64_t n = k * x.slots / (workgroups_of_rows((int64_t)x.chunk_len * (x.h_q / x.h_kv), pairing) * (int64_t)x.h_kv);
-      if (n > 16 && n <= max_n) consider(n);
+  auto each_count = [&](auto&& visit) {
+    for (int64_t n = 2; n <= std::min<int64_t>(16, max_n); ++n) visit(n);
+    for (int64_t k = 1; max_n > 16 && k * x.slots <= kSplitWgsMany; ++k) {
+      for (const int p : {kMirrored, kSingle, kShort}) {
+        const int64_t n = k * x.slots / (workgroups_of_rows((int64_t)x.chunk_len * (x.h_q / x.h_kv), p) * (int64_t)x.h_kv);
+        if (n > 16 && n <= max_n) visit(n);
+      }
     }
-  }
+  };
+  // The most promising count first: what it takes rules most others out.
+  int64_t first = 0;
+  double first_us = INFINITY;
+  each_count([&](int64_t n) {
+    const double us = model.least((int)n);
+    if (us < first_us) {
+      first_us = us;
+      first = n;
+    }
+  });
+  if (first > 0) consider(first);
+  each_count(consider);
   std::lock_guard<std::mutex> lock(g_plan_mutex);
   g_plan_keys[g_plan_next] = key;
-  g_plan_values[g_plan_next] = best;
+  g_plan_values[g_plan_next] = {best, pairing};
   g_plan_next = (g_plan_next + 1) % kPlanCache;
   if (g_plan_count < kPlanCache) ++g_plan_count;
+  *pairing_out = pairing;
   return best;
 }
 
@@ -360,7 +549,7 @@ mocap_status make_plan(int64_t prefix_len, int32_t chunk_len, int32_t h_q, int32
     if (st != MOCAP_OK) return st;
   }
   const LaunchShape x{prefix_len, chunk_len, h_q, h_kv, head_dim, plan->row_groups, cus};
-  plan->n_ranges = choose_ranges(x, plan->base_wgs, plan->prefix_tiles, num_splits, ws_cap);
+  plan->n_ranges = choose_ranges(x, plan->base_wgs, plan->prefix_tiles, num_splits, ws_cap, &plan->pairing);
   plan->own_range = num_splits > 1;
   plan->ws_bytes = workspace_for(plan->n_ranges, chunk_len, h_q, head_dim);
   return MOCAP_OK;
@@ -410,7 +599,7 @@ bool valid_remote_range(int64_t begin, int64_t end, int64_t prefix_len) {
   return begin >= 0 && begin <= end && end <= prefix_len && begin % kTileKeys == 0 && end % kTileKeys == 0;
 }
 
-// Pairing of row groups for a launch (best_pairing_us), cached per shape.
+// Pairing of row groups for a launch whose ranges were not chosen here, cached per shape.
 struct PairKey {
   int64_t prefix_len;
   int32_t chunk_len, h_q, h_kv, head_dim, n_ranges, slots, mode;
@@ -433,9 +622,8 @@ int choose_pairing(const Plan& plan, int64_t prefix_len, int32_t chunk_len, int3
     for (int i = 0; i < g_pair_count; ++i)
       if (g_pair_keys[i] == key) return g_pair_values[i];
   }
-  int pairing = kMirrored;
-  best_pairing_us(LaunchShape{prefix_len, chunk_len, h_q, h_kv, head_dim, plan.row_groups, std::max(cus, 1)},
-                  plan.n_ranges, plan.own_range, &pairing);
+  const LaunchShape x{prefix_len, chunk_len, h_q, h_kv, head_dim, plan.row_groups, std::max(cus, 1)};
+  const int pairing = LaunchModel(x, plan.own_range).best(plan.n_ranges, INFINITY, pairing_mode(), nullptr);
   std::lock_guard<std::mutex> lock(g_plan_mutex);
   g_pair_keys[g_pair_next] = key;
   g_pair_values[g_pair_next] = pairing;
@@ -482,7 +670,8 @@ mocap_status prepare_attention(const mocap_kv_store* kv, const int32_t* block_ta
   p.group = h_q / h_kv;
   block_divider((uint32_t)p.group, &p.group_magic, &p.group_shift);
   p.row_groups = plan.row_groups;
-  {
+  p.pairing = plan.pairing;
+  if (p.pairing < 0) {
     int cus = 0;
     const mocap_status st = device_cu_count(&cus);
     if (st != MOCAP_OK) return st;

@@ -1,6 +1,6 @@
 // A CPU build of the library's host side (api.cpp, plan.cpp, lse_merge.hip) in
-// which every launch is recorded and none is made: the device has the number of
-// compute units that record_cus sets.
+// which every launch is recorded and none is made, on a device of 256 compute
+// units.
 #include <hip/hip_runtime.h>
 
 #include <vector>
@@ -10,7 +10,7 @@
 namespace {
 std::vector<mocap::AttnLaunch> attn;  // of the attention launches, in order
 std::vector<unsigned> dims;           // grid and block of the merge launches, 6 numbers each
-int launches = 0, cus = 256;
+int launches = 0;
 }  // namespace
 
 namespace mocap {
@@ -33,7 +33,7 @@ hipError_t hipGetDevice(int* dev) {
   return hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int* value, hipDeviceAttribute_t, int) {
-  *value = cus;
+  *value = 256;
   return hipSuccess;
 }
 hipError_t hipGetSymbolAddress(void** ptr, const void*) {
@@ -48,7 +48,6 @@ hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t
 }
 hipError_t hipGetLastError() { return hipSuccess; }
 
-void record_cus(int n) { cus = n; }  // before the first call
 int record_launches() { return launches; }
 // The last attention launch: placement, ranges, workgroups.
 void record_last(int* out) {

@@ -4,6 +4,7 @@ import ctypes
 import heapq
 import math
 import random
+import time
 
 import pytest
 
@@ -137,3 +138,35 @@ def test_placement_of_requested_ranges(host_lib, shape, splits):
     placement, n = library_choice(host_lib, *shape, splits=splits)
     assert n == min(splits, -(-shape[0] // 64) + 1)
     assert placement == best_placement(*shape, n, n > 1)[0]
+
+
+@pytest.mark.parametrize("shape", shapes(12, 8, 300) + [(2000000, 60, 64, 8, 128)])
+def test_noalloc_takes_the_same_plan_if_it_fits(host_lib, shape):
+    prefix, length, h_q, h_kv, d = shape
+    want = library_choice(host_lib, *shape)
+    rows = want[1] * length * h_q
+    store = binding.mocap_kv_store(FAKE, FAKE, 1 << 22, 64, h_kv, d)
+    assert host_lib.mocap_chunk_attn_noalloc(ctypes.byref(store), FAKE, 1 << 22, FAKE, prefix, length, h_q, h_kv, d,
+                                             0.1, FAKE, FAKE, 0, None) == 0
+    out = (ctypes.c_int * 3)()
+    host_lib.record_last(out)
+    if rows * (d + 1) * 4 + 512 <= 128 << 20:
+        assert (out[0], out[1]) == want
+    else:
+        assert out[1] * length * h_q * (d + 1) * 4 <= 128 << 20
+
+
+@pytest.mark.parametrize("shape", [
+    (1000000, 1, 32, 1, 128), (119040, 19, 64, 1, 64), (438570, 5, 8, 2, 128), (102400, 119, 32, 1, 128),
+    (788329, 3, 6, 3, 128), (886504, 34, 16, 2, 64), (865010, 188, 12, 4, 128),
+])
+def test_a_new_shape_is_planned_quickly(host_lib, shape):
+    """Short chunks behind long prefixes, whose planning must not take longer than the launch: 11 to 60 us each
+    (200 to 490 with every candidate walked through, 16 to 68 with the few candidates of one range count each that
+    were once looked at).  The best of nine prefixes not planned before, against twice the slowest."""
+    times = []
+    for i in range(9):
+        t = time.perf_counter()
+        library_choice(host_lib, shape[0] + 1 + i, *shape[1:])
+        times.append(time.perf_counter() - t)
+    assert min(times) < 120e-6, [round(x * 1e6) for x in times]
