@@ -152,7 +152,7 @@ int workgroups_of_rows(int64_t rows, int pairing) {
 // bounds made without any of that leave few candidates to walk through.
 // Planning a new shape, up to 512 tokens behind up to 10^6 keys: 12 us on
 // average, 63 at the 99th percentile; with an array of all costs and a heap for
-// every candidate 72 and 450.
+// every candidate 72 and 450.  Up to 8192 tokens: 18 us against 92.
 class LaunchModel {
  public:
   LaunchModel(const LaunchShape& x, bool own_range)
@@ -182,9 +182,8 @@ class LaunchModel {
     // With up to two row groups the two ways to pair them are the same, with
     // one so is single.
     const int64_t groups = layout_[kMirrored].units;
-    const bool open[4] = {true, groups > 2,
-                          groups > 1 && layout_[kSingle].wgs * x_.h_kv * n_ranges <= kSingleRounds * x_.slots,
-                          layout_[kShort].wgs * x_.h_kv * n_ranges <= kShortRounds * x_.slots};
+    const bool open[4] = {true, groups > 2, groups > 1 && few_enough(kSingle, n_ranges),
+                          few_enough(kShort, n_ranges)};
     constexpr double bar[4] = {1.0, 0.98, 0.98, 0.95};
     double lo[4], hi[4];  // the time lies between
     double least = INFINITY;
@@ -229,7 +228,8 @@ class LaunchModel {
   // A lower bound of the time of any placement.
   double least(int n_ranges) const {
     double us = INFINITY;
-    for (int p : {kMirrored, kAdjacent, kSingle, kShort}) us = std::min(us, bound(p, n_ranges));
+    for (int p : {kMirrored, kAdjacent, kSingle, kShort})
+      if (few_enough(p, n_ranges)) us = std::min(us, bound(p, n_ranges));
     return us;
   }
 
@@ -242,6 +242,11 @@ class LaunchModel {
     bool lone;      // the last of them has one row group where the others have two
     double work;    // tiles of one KV head's workgroups over the whole span, in units of kTileUs
   };
+
+  bool few_enough(int pairing, int64_t n_ranges) const {
+    const int64_t rounds = pairing == kSingle ? kSingleRounds : pairing == kShort ? kShortRounds : INT64_MAX / x_.slots;
+    return layout_[pairing].wgs * x_.h_kv * n_ranges <= rounds * x_.slots;
+  }
 
   // The end of the tiles that row group (or slot) u sees.
   int64_t unit_end(int64_t u, int unit_rows) const {
@@ -273,6 +278,7 @@ class LaunchModel {
     // of the prefix's end twice if the chunk's keys are a range of their own).
     const int64_t twice = own_ ? span_ - x_.prefix_len / kTileKeys : 0;
     l.work = 0.0;
+    if (!few_enough(pairing, 1)) return;  // is never looked at
     for (int64_t q = 0; q < l.wgs; ++q) {
       int64_t top, other;
       groups_of(pairing, q, &top, &other);
