@@ -32,6 +32,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 // 17.2 and 16.6, 576 x 16 35.6 and 35.8, 4096 x 20 238 and 242.
 constexpr int kLoadsMany = 4, kLoadsFew = 8;
 constexpr int64_t kFewRows = 512;
+constexpr int64_t kMaxGroupsX = ((int64_t)1 << 32) / kGroupThreads - 1;
 
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
@@ -50,7 +51,7 @@ __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLau
   constexpr int QUADS = D / 4;         // lanes that hold one partial row
   constexpr int PARTS = 64 / QUADS;    // ranges a wavefront reads at a time
   const int lane = threadIdx.x & 63;
-  const int64_t rh = (int64_t)blockIdx.x * kWavesPerGroup + (threadIdx.x >> 6);
+  const int64_t rh = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kWavesPerGroup + (threadIdx.x >> 6);
   const int64_t L = p.chunk_len;
   if (rh >= L * p.h_q) return;         // a whole wavefront: no barrier follows
   const int head = (int)(rh % p.h_q);  // row-major over (row, head)
@@ -121,7 +122,11 @@ __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLau
 
 hipError_t launch_lse_merge(const MergeLaunch& p, int head_dim, hipStream_t stream) {
   const int64_t rows = (int64_t)p.chunk_len * p.h_q;
-  const dim3 grid((unsigned)((rows + kWavesPerGroup - 1) / kWavesPerGroup)), block(kGroupThreads);
+  // A dimension of a grid holds fewer than 2^32 threads (2^26 rows); more go
+  // to its second dimension.
+  const int64_t groups = (rows + kWavesPerGroup - 1) / kWavesPerGroup;
+  const int64_t layers = (groups + kMaxGroupsX - 1) / kMaxGroupsX;
+  const dim3 grid((unsigned)((groups + layers - 1) / layers), (unsigned)layers), block(kGroupThreads);
   const bool few = rows <= kFewRows;
   if (head_dim == 128) {
     if (few) {

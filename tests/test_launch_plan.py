@@ -170,3 +170,19 @@ def test_a_new_shape_is_planned_quickly(host_lib, shape):
         library_choice(host_lib, shape[0] + 1 + i, *shape[1:])
         times.append(time.perf_counter() - t)
     assert min(times) < 120e-6, [round(x * 1e6) for x in times]
+
+
+@pytest.mark.parametrize("length,h_q", [(1, 1), (7, 32), (2**20, 64), (2**20 + 3, 64), (2**24, 8), (2**22, 256)])
+def test_merge_grid_holds_every_row(host_lib, length, h_q):
+    """Up to the largest chunk that is accepted; a dimension of a grid takes fewer than 2^32 threads."""
+    ranges, size = ctypes.c_int32(), ctypes.c_size_t()
+    store = binding.mocap_kv_store(FAKE, FAKE, 1 << 22, 64, 1, 64)
+    assert host_lib.mocap_chunk_attn_workspace_size(64, length, h_q, 1, 64, 2, ctypes.byref(ranges), ctypes.byref(size)) == 0
+    assert host_lib.mocap_chunk_attn(ctypes.byref(store), FAKE, 1 << 22, FAKE, 64, length, h_q, 1, 64, 0.1, FAKE, FAKE,
+                                     FAKE, size.value, 2, None) == 0
+    out = (ctypes.c_uint * 6)()
+    host_lib.record_merge(out)
+    gx, gy, gz, bx, by, bz = out
+    assert (gz, by, bz) == (1, 1, 1) and gx * bx < 2**32 and gy < 2**16
+    assert gx * gy * bx >= length * h_q * 64  # a wavefront of 64 threads per row
+    assert gx * gy * bx < (length * h_q + 4 * gy) * 64 + bx
