@@ -108,16 +108,20 @@ class ChunkedPrefill:
 
     def _one_call(self, q, k, v) -> bool:
         """Whether the whole sequence can go to the library in one call: one
-        store, the chunks as planned, nothing of this class replaced, tables not
-        checked call by call, and whole inputs of which every chunk's slice
-        would be accepted (anything else takes, or fails in, the loop)."""
+        store, the chunks as planned, no method of this class and no call of the
+        binding that the loop would make replaced (a tracer's wrapper sees every
+        chunk), tables not checked call by call, and whole tensors of which every
+        chunk's slice would be accepted (anything else takes, or fails in, the
+        loop)."""
         if self.remote is not None or binding._check_tables or not self.lengths:
             return False
-        if type(self) is not ChunkedPrefill or not vars(self).keys().isdisjoint(("append", "attend", "lse")):
+        if type(self) is not ChunkedPrefill or not vars(self).keys().isdisjoint(_LOOP_METHODS):
+            return False
+        if _loop_parts() != _LOOP_PARTS:
             return False
         if (self.lengths, self.prefixes) != self._planned:
             return False
-        for t, heads in ((q, self.h_q), (k, self.h_kv), (v, self.h_kv)):
+        for t, heads in ((q, self.h_q), (k, self.h_kv), (v, self.h_kv), (self.o, self.h_q)):
             if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous()
                     and t.dim() == 3 and t.shape[0] >= self.seq_len and t.shape[1] == heads
                     and t.shape[2] == self.head_dim):
@@ -145,3 +149,15 @@ class ChunkedPrefill:
             if events is not None:
                 events[c][2].record(stream)
         return self.o
+
+
+_LOOP_METHODS = ("append", "attend", "lse", "remote_range")
+
+
+def _loop_parts():
+    """What a chunk's turn of the loop is made of."""
+    c = ChunkedPrefill
+    return c.append, c.attend, c.lse, c.remote_range, binding.mocap_kv_append, binding.mocap_chunk_attn
+
+
+_LOOP_PARTS = _loop_parts()

@@ -126,3 +126,40 @@ def test_inputs_the_loop_refuses_stay_refused(gpu):
             binding.mocap_chunk_prefill(r.store, r.table, lengths, q, k, v, 0.1, r.o, r._lse_flat, r.workspace)
     assert torch.equal(r.store.k_pool.view(torch.int16), before[0])
     assert torch.equal(r.store.v_pool.view(torch.int16), before[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("owner,name", [
+    (ChunkedPrefill, "append"), (ChunkedPrefill, "attend"), (ChunkedPrefill, "lse"),
+    (binding, "mocap_kv_append"), (binding, "mocap_chunk_attn"), (None, "attend"),
+])
+def test_replaced_calls_are_made(gpu, monkeypatch, owner, name):
+    """A wrapper around a method (of the class or of one object) or around a call of the binding sees every chunk."""
+    r = ChunkedPrefill(8, 2, 64, [64, 50, 14], block_size=64)
+    q, k, v = (t.cuda() for t in synth.make_qkv(97, 128, 8, 2, 64))
+    calls = []
+    original = getattr(owner or r, name)
+
+    def wrapper(*args, **kwargs):
+        calls.append(name)
+        return original(*args, **kwargs)
+    assert r._one_call(q, k, v)
+    want = r.run(q, k, v, 0.1).clone()
+    assert not calls
+    with monkeypatch.context() as patch:
+        patch.setattr(owner or r, name, wrapper)
+        got = r.run(q, k, v, 0.1)
+        assert calls == [name] * 3
+        assert torch.equal(got, want)
+    if owner is not None:
+        assert r._one_call(q, k, v)
+
+
+@pytest.mark.gpu
+def test_an_output_only_the_loop_accepts(gpu):
+    """One-token chunks of an O with a longer row stride: each slice is contiguous, the whole is not."""
+    r = ChunkedPrefill(4, 2, 64, [1, 1, 1], block_size=64)
+    q, k, v = (t.cuda() for t in synth.make_qkv(98, 3, 4, 2, 64))
+    want = r.run(q, k, v, 0.125).clone()
+    r.o = torch.zeros(3, 8, 64, dtype=torch.bfloat16, device="cuda")[:, :4]
+    assert torch.equal(r.run(q, k, v, 0.125), want)
