@@ -184,10 +184,16 @@ def _check(status: int, where: str):
         raise MocapError(status, where)
 
 
+# The current stream's handle without the Stream object around it, where this
+# torch has it (0.3 us against 2.7); torch.cuda.current_stream() otherwise.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
-        # The current stream's handle without the Stream object around it.
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 

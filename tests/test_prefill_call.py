@@ -163,3 +163,15 @@ def test_an_output_only_the_loop_accepts(gpu):
     want = r.run(q, k, v, 0.125).clone()
     r.o = torch.zeros(3, 8, 64, dtype=torch.bfloat16, device="cuda")[:, :4]
     assert torch.equal(r.run(q, k, v, 0.125), want)
+
+
+@pytest.mark.gpu
+def test_current_stream_handle(gpu, monkeypatch):
+    """The handle of the current stream, also in a torch without the raw accessor."""
+    side = torch.cuda.Stream()
+    for raw in (binding._raw_stream, None):
+        monkeypatch.setattr(binding, "_raw_stream", raw)
+        assert binding._stream_handle(None) == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert binding._stream_handle(None) == side.cuda_stream
+        assert binding._stream_handle(side) == side.cuda_stream
