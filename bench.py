@@ -75,23 +75,40 @@ def parse():
     return ap.parse_args()
 
 
+# What the attention kernels are compiled from.
+KERNEL_SOURCES = ("chunk_attn.hip", "chunk_attn_short.hip", "attn_device.h", "internal.h")
+
+
+def kernel_sources_sha256():
+    import hashlib
+    digest = hashlib.sha256()
+    for name in KERNEL_SOURCES:
+        with open(os.path.join(ROOT, "paper_2606_22968_amd", "csrc", name), "rb") as f:
+            digest.update(f.read())
+    return digest.hexdigest()
+
+
+def attention_kernels(w, lengths, two_stores, cus):
+    """The attention kernels a step may launch.  The planner gives a chunk to the short kernel only where its
+    32-row workgroups are at most four per compute unit."""
+    args = f"<{w.head_dim}, {'true' if two_stores else 'false'}>"
+    short = [n * w.h_q <= 4 * cus * 32 for n in lengths if n > 0]
+    names = [f"chunk_attn_kernel{args}"]
+    return " or ".join(names + [f"chunk_attn_short_kernel{args}"] if any(short) else names)
+
+
 def recorded_counters(workload):
     """Counter figures of the attention kernel from the committed rocprofv3
     summary of this workload (HBM bytes per launch from FETCH_SIZE and
     WRITE_SIZE scaled by a device-copy calibration; average clock from
-    GRBM_GUI_ACTIVE), or None when there is none or the kernel source changed
-    since the counters were taken."""
-    import hashlib
+    GRBM_GUI_ACTIVE), or None when there is none or one of the kernel's sources
+    changed since the counters were taken."""
     path = os.path.join(ROOT, "profiles", f"chunk_attn_{workload}_counters.json")
-    src = os.path.join(ROOT, "paper_2606_22968_amd", "csrc", "chunk_attn.hip")
     if not os.path.exists(path):
         return None
     with open(path) as f:
         rec = json.load(f)
-    with open(src, "rb") as f:
-        if hashlib.sha256(f.read()).hexdigest() != rec.get("kernel_source_sha256"):
-            return None
-    return rec
+    return rec if rec.get("kernel_sources_sha256") == kernel_sources_sha256() else None
 
 
 def causal_pairs(lengths):
@@ -213,7 +230,6 @@ def summarize_counters(root, workload, steps, calib_mib):
     GRBM_GUI_ACTIVE per die against each launch's duration, which removes the
     fixed per-dispatch part of the counter window."""
     import glob
-    import hashlib
     from paper_2606_22968_amd import binding, synth
     w = synth.WORKLOADS[workload]
     lengths = binding.mocap_chunk_plan(w.seq_len, w.num_chunks, w.align, balanced=(w.chunking == "balanced"))
@@ -224,7 +240,7 @@ def summarize_counters(root, workload, steps, calib_mib):
         if len(files) != 1:
             raise SystemExit(f"{root}/{sub}: expected one counter_collection.csv, found {len(files)}")
         rows = _counter_rows(files[0])
-        attn = list(_per_dispatch(rows, "chunk_attn_kernel").values())
+        attn = list(_per_dispatch(rows, "chunk_attn_").values())  # tiled and short
         if len(attn) < n:
             raise SystemExit(f"{files[0]}: {len(attn)} attention launches, fewer than {steps} x {len(lengths)}")
         copies = list(_per_dispatch(rows, "copyBuffer").values())
@@ -257,13 +273,12 @@ def summarize_counters(root, workload, steps, calib_mib):
     for a in append:
         for k, v in a[1].items():
             app[k] = app.get(k, 0.0) + v
-    src = os.path.join(ROOT, "paper_2606_22968_amd", "csrc", "chunk_attn.hip")
-    with open(src, "rb") as f:
-        sha = hashlib.sha256(f.read()).hexdigest()
+    sha = kernel_sources_sha256()
     rec = {
-        "kernel": attn[0][0],
+        "kernel": ", ".join(sorted({a[0] for a in attn})),
         "workload": workload,
-        "kernel_source_sha256": sha,
+        "kernel_sources": list(KERNEL_SOURCES),
+        "kernel_sources_sha256": sha,
         "launches": n,
         "calibration_copy_bytes": calib_bytes,
         "fetch_scale": scales["FETCH_SIZE"],
@@ -286,7 +301,7 @@ def summarize_counters(root, workload, steps, calib_mib):
         json.dump(rec, f, indent=1)
     mfma = sums.get("SQ_INSTS_MFMA", 0.0)
     busy_cycles = sum(cyc)
-    print(f"kernel: {rec['kernel']} ({n} launches of the timed step(s)); source sha256 {sha[:16]}")
+    print(f"kernel: {rec['kernel']} ({n} launches of the timed step(s)); sources sha256 {sha[:16]}")
     print(f"calibration copy {calib_bytes / 2**20:.0f} MiB: FETCH_SIZE x {scales['FETCH_SIZE']:.4f}, "
           f"WRITE_SIZE x {scales['WRITE_SIZE']:.4f}")
     print(f"HBM bytes per launch: fetched {per_launch['FETCH_SIZE']:.4e}, written {per_launch['WRITE_SIZE']:.4e}, "
@@ -428,7 +443,8 @@ def main():
         "causal_flops_per_step": flops,
         "roofline": {
             "bound": "mfma",
-            "kernel": f"chunk_attn_kernel<{w.head_dim}, {'true' if runner.remote else 'false'}>",
+            "kernel": attention_kernels(w, lengths, bool(runner.remote),
+                                        torch.cuda.get_device_properties(0).multi_processor_count),
             "achieved": round(achieved, 2),
             "peak": MFMA_BF16_PEAK_TFLOPS,
             "unit": "TFLOP/s",
