@@ -26,3 +26,14 @@ def test_merge_few_and_many_rows(gpu, oracle_lib, length):
     q, k, v = synth.make_qkv(92, 2048 + length, 4, 2, 64)
     runner = run_gpu(q, k, v, [2048, length], 0.125, block_size=64, num_splits=21)
     check_chunks(oracle_lib, runner, q, k, v, 0.125, rows_of=lambda c, n: [0, 1, 63, n - 1], label=f"rows={4 * length}")
+
+
+@pytest.mark.parametrize("h_q,h_kv,d", [(4, 1, 128), (4, 4, 64)])
+@pytest.mark.parametrize("splits", [63, 64, 65, 129])
+def test_merge_many_rows_of_many_ranges(gpu, oracle_lib, splits, h_q, h_kv, d):
+    """520 rows: the loads of many rows, below, at and above 64 ranges at a time."""
+    q, k, v = synth.make_qkv(93, 8300 + 130, h_q, h_kv, d)
+    runner = run_gpu(q, k, v, [8300, 130], d ** -0.5, block_size=64, num_splits=splits)
+    assert runner.splits[1] == splits
+    check_chunks(oracle_lib, runner, q, k, v, d ** -0.5, rows_of=lambda c, n: [0, 1, 63, 64, n - 1],
+                 label=f"rows=520 splits={splits}")

@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from helpers import check_chunks, run_gpu, say
-from paper_2606_22968_amd import synth
+from paper_2606_22968_amd import binding, synth
 from paper_2606_22968_amd.prefill import ChunkedPrefill
 
 pytestmark = pytest.mark.gpu
@@ -24,45 +24,63 @@ PLACEMENTS = ["mirrored", "adjacent", "single", "short"]
     (64, 1, 64, [1, 2, 3, 40]),                  # a token's heads over two slots
     (40, 1, 128, [1, 3, 70]),                    # groups that share a slot with the next token's
 ])
-@pytest.mark.parametrize("splits", [1, 3, 0])
+@pytest.mark.parametrize("splits", [1, 2, 3, 0])
 def test_rows_and_keys_at_edges(gpu, oracle_lib, monkeypatch, placement, h_q, h_kv, d, lengths, splits):
     monkeypatch.setenv("MOCAP_PAIRING", placement)
     say(f"[case] placement={placement} h_q={h_q} h_kv={h_kv} d={d} splits={splits}")
     q, k, v = synth.make_qkv(70 + h_q, sum(lengths), h_q, h_kv, d)
     scale = d ** -0.5
     runner = run_gpu(q, k, v, lengths, scale, block_size=64, num_splits=splits, pool_fill=float("nan"))
+    assert splits == 0 or runner.splits[-1] == min(splits, (sum(lengths[:-1]) + 63) // 64 + 1)
     check_chunks(oracle_lib, runner, q, k, v, scale, label=f"{placement} splits={splits}")
+
+
+def _first_chunk_sampled(c, n):
+    return [0, 1, 63, 64, n // 2, n - 1] if c == 0 else None
 
 
 @pytest.mark.parametrize("placement", PLACEMENTS)
 @pytest.mark.parametrize("h_q,h_kv,d,lengths", [
-    (4, 2, 128, [1100, 5, 17, 700]),
-    (16, 2, 64, [1000, 13, 130]),
+    (4, 2, 128, [5000, 5, 17, 33]),
+    (16, 2, 64, [9001, 13, 130, 40]),
+    (32, 8, 128, [9001, 7]),
+    (8, 8, 64, [4000, 64, 3]),
 ])
 def test_even_ranges_two_stores(gpu, oracle_lib, monkeypatch, placement, h_q, h_kv, d, lengths):
-    """Automatic plans, with and without a second store: the same bits."""
+    """Automatic plans that are split, with one store, with two, and through the no-allocation call: the same bits."""
     monkeypatch.setenv("MOCAP_PAIRING", placement)
-    q, k, v = synth.make_qkv(80 + h_q, sum(lengths), h_q, h_kv, d)
+    S = sum(lengths)
+    q, k, v = synth.make_qkv(80 + h_q, S, h_q, h_kv, d)
     scale = d ** -0.5
     one = run_gpu(q, k, v, lengths, scale, block_size=128, pool_fill=float("nan"))
     say(f"[case] placement={placement} splits={one.splits}")
-    check_chunks(oracle_lib, one, q, k, v, scale, label=f"{placement} {one.splits}")
+    assert min(one.splits[1:]) > 2
+    check_chunks(oracle_lib, one, q, k, v, scale, rows_of=_first_chunk_sampled, label=f"{placement} {one.splits}")
     two = run_gpu(q, k, v, lengths, scale, runner=ChunkedPrefill(
         h_q, h_kv, d, lengths, block_size=128, pool_fill=float("nan"), remote=(128, 960)))
     assert two.splits == one.splits
-    assert torch.equal(one.o.view(torch.int16), two.o.view(torch.int16))
+    for c, p in enumerate(one.prefixes):
+        n = lengths[c]
+        o, lse = torch.empty_like(one.o[p:p + n]), torch.empty_like(one.lse(c))
+        binding.mocap_chunk_attn_noalloc(one.store, one.table, q[p:p + n].cuda(), p, scale, o, lse)
+        torch.cuda.synchronize()
+        for got_o, got_lse in ((two.o[p:p + n], two.lse(c)), (o, lse)):
+            assert torch.equal(got_o.view(torch.int16), one.o[p:p + n].view(torch.int16))
+            assert torch.equal(got_lse, one.lse(c))
 
 
+@pytest.mark.parametrize("splits", [1, 4, 0])
 @pytest.mark.parametrize("d", [64, 128])
-def test_short_kernel_overflow_rescale(gpu, oracle_lib, monkeypatch, d):
+def test_short_kernel_overflow_rescale(gpu, oracle_lib, monkeypatch, d, splits):
     """Scores that grow by more than 60 binary orders from step to step."""
     monkeypatch.setenv("MOCAP_PAIRING", "short")
-    lengths = [600, 40]
+    lengths = [5000, 40]
     q, k, v = synth.make_qkv(91, sum(lengths), 4, 1, d)
     q[:, :, 0] = 8.0
-    for at, grow in ((10, 8.0), (45, 80.0), (300, 160.0), (310, 240.0), (630, 320.0)):
+    for at, grow in ((10, 8.0), (45, 80.0), (300, 160.0), (310, 240.0), (3100, 280.0), (5030, 320.0)):
         k[at, :, 0] = grow
     scale = d ** -0.5 if d == 64 else 0.125
-    for splits in (1, 0):
-        runner = run_gpu(q, k, v, lengths, scale, block_size=64, num_splits=splits)
-        check_chunks(oracle_lib, runner, q, k, v, scale, label=f"rescale d={d} splits={splits}")
+    runner = run_gpu(q, k, v, lengths, scale, block_size=64, num_splits=splits)
+    assert runner.splits[1] == splits or (splits == 0 and runner.splits[1] > 1)
+    check_chunks(oracle_lib, runner, q, k, v, scale, rows_of=lambda c, n: [0, 9, 10, 11, 45, 46, 309, 310, 3099, 4999]
+                 if c == 0 else None, label=f"rescale d={d} splits={runner.splits}")
