@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kGroupThreads) void lse_merge_kernel(const MergeLau
         const bool used = i < n && !(wi < 0.f);
         wi = used ? wi : 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] += wi * (used ? v[j][e] : 0.f);
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(wi, used ? v[j][e] : 0.f, acc[e]);
       }
     }
   }
