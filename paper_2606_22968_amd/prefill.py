@@ -117,11 +117,11 @@ class ChunkedPrefill:
             return False
         if type(self) is not ChunkedPrefill or not vars(self).keys().isdisjoint(_LOOP_METHODS):
             return False
-        if _loop_parts() != _LOOP_PARTS:
+        if _loop_parts() != _LOOP_PARTS or not self.o.is_contiguous():
             return False
         if (self.lengths, self.prefixes) != self._planned:
             return False
-        for t, heads in ((q, self.h_q), (k, self.h_kv), (v, self.h_kv), (self.o, self.h_q)):
+        for t, heads in ((q, self.h_q), (k, self.h_kv), (v, self.h_kv)):
             if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous()
                     and t.dim() == 3 and t.shape[0] >= self.seq_len and t.shape[1] == heads
                     and t.shape[2] == self.head_dim):
