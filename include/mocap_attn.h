@@ -46,11 +46,17 @@
  *     MOCAP_ERR_INVALID_ARG, launching nothing, when one is out of range or
  *     two logical blocks share a physical block.
  *   - All device pointers must be 16-byte aligned.
- *   - The attention calls choose, per launch and from a time model, how the
- *     two halves of a workgroup pair up query rows; the environment variable
- *     MOCAP_PAIRING=mirrored or =adjacent forces one choice (for testing).
- *     Results agree with the oracle either way; they need not be bitwise
- *     equal between the two.
+ *   - The attention calls choose, per launch and from a time model, the kernel
+ *     and how a chunk's rows are placed in workgroups; for num_splits = 0 the
+ *     number of KV ranges follows from the same model.  The environment
+ *     variable MOCAP_PAIRING forces one placement (for testing): mirrored,
+ *     adjacent or single of the tiled kernel, or short, the kernel for chunks
+ *     of few rows.  It changes the automatic ranges and so the workspace size:
+ *     it must not change between mocap_chunk_attn_workspace_size and the call.
+ *     Results agree with the oracle whatever is chosen; they need not be
+ *     bitwise equal between two choices.
+ *   - NaN propagates: a query row that sees a NaN score has NaN in all of O and
+ *     in its LSE.
  */
 #ifndef MOCAP_ATTN_H
 #define MOCAP_ATTN_H

@@ -15,8 +15,8 @@
 //     32 / G neighbouring tokens, which keeps its masked tiles few.  With
 //     rows counted per query head instead (64 tokens of two heads per unit),
 //     137 tokens of 4 heads filled 137 of 256 slots, now 548 of 768:
-//     behind 30720 tokens 113 -> 90 us; 300 tokens behind 2^20 5.5 -> 4.7 ms;
-//     2048-token chunks within 0.5%.
+//     behind 30720 tokens 113 -> 93 us; 300 tokens behind 2^20 5.7 -> 4.8 ms;
+//     2048-token chunks unchanged (within the runs' spread).
 //   * Causal balance: the workgroup's two units of four waves take two row
 //     groups of the same KV head, r and R-1-r (mirrored, so every
 //     workgroup carries about the same number of (row, key) pairs), two
