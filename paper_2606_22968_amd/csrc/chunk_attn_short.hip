@@ -282,13 +282,12 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_short_kernel(const
 #pragma unroll
   for (int w = 0; w < kAttnWaves; ++w) m = fmaxf(m, part_m[w][l32]);
   float weight[kAttnWaves], l = 0.f, f = 0.f;
-  uint32_t counts = 0;
+  bool counts[kAttnWaves];
 #pragma unroll
   for (int w = 0; w < kAttnWaves; ++w) {
     const float l_w = part_l[w][l32];
-    const bool any = l_w != 0.f;
-    counts |= any ? 1u << w : 0u;
-    weight[w] = any ? __builtin_amdgcn_exp2f(part_m[w][l32] - m) : 0.f;
+    counts[w] = l_w != 0.f;
+    weight[w] = counts[w] ? __builtin_amdgcn_exp2f(part_m[w][l32] - m) : 0.f;
     l += l_w * weight[w];
     f += part_f[w][l32] * weight[w];
   }
@@ -306,7 +305,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void chunk_attn_short_kernel(const
       const f32x4 o_w = reinterpret_cast<const f32x4*>(ring[w])[piece * 64 + lane];
       // The ring of a wavefront without steps holds anything.
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] += weight[w] * ((counts >> w & 1u) != 0 ? o_w[e] : 0.f);
+      for (int e = 0; e < 4; ++e) o[e] += weight[w] * (counts[w] ? o_w[e] : 0.f);
     }
     o *= inv;
     const int dim = piece * 8 + half * 4;  // (md, j) covers dims md * 32 + j * 8
