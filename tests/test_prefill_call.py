@@ -167,10 +167,12 @@ def test_an_output_only_the_loop_accepts(gpu):
 
 @pytest.mark.gpu
 def test_current_stream_handle(gpu, monkeypatch):
-    """The handle of the current stream, also in a torch without the raw accessor."""
+    """The handle of the current stream, also in a torch without the raw accessors."""
     side = torch.cuda.Stream()
-    for raw in (binding._raw_stream, None):
+    for raw, device in ((binding._raw_stream, binding._raw_device), (binding._raw_stream, torch.cuda.current_device),
+                        (None, torch.cuda.current_device)):
         monkeypatch.setattr(binding, "_raw_stream", raw)
+        monkeypatch.setattr(binding, "_raw_device", device)
         assert binding._stream_handle(None) == torch.cuda.current_stream().cuda_stream
         with torch.cuda.stream(side):
             assert binding._stream_handle(None) == side.cuda_stream
